@@ -53,7 +53,7 @@ OPS_PRECULL = 485.0  # per particle the batched path's seeding estimate removes:
                      # FP32 normal-speed estimate, start and two Halley steps (105) + the latitude from the fine
                      # table (25) + frame, Box-Muller and angles (50) + grown two-box test (55), in place of
                      # OPS_SEED and the one root-node visit such a particle costs on the plain path
-KERNEL_SOURCES = ["tpmc_device.hpp", "tpmc_math.hpp", "tpmc_kernels.hip", "tpmc_internal.h"]
+KERNEL_SOURCES = ["tpmc_device.hpp", "tpmc_math.hpp", "tpmc_units.hpp", "tpmc_kernels.hip", "tpmc_internal.h"]
 
 
 def log(*a):
@@ -1101,7 +1101,7 @@ def served_measure(args, n_warm, n_meas, load_fracs, fifo_requests):
     # tiles of 16384 particles and a refill threshold of 32 lanes: the tuner, timing one batch,
     # cannot see the per-step costs of claiming tiles (smaller tiles) and of the last tiles of a
     # step (larger ones), nor how a step's mix of meshes shares the waves.  Measured on the
-    # pipelined stream at saturation (2000 requests, work claimed per wave in quarter tiles):
+    # pipelined stream at saturation (2000 requests, work claimed per wave):
     # tiles 16384 / 32768 / 65536 gave 4505 / 4439 / 3996 req/s; refill 16 / 24 / 32 / 40 / 48
     # lanes gave 4091 / 4135 / 4171 / 4069 / 3815 req/s and workgroups per CU 4 / 8 / 16 at
     # refill 32 gave 4171 / 4176 / 4163 (workgroup tiles, 1000 requests).

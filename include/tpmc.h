@@ -161,9 +161,11 @@ typedef struct {
                               (re-emission, tallies, next segment or particle) once fewer than this
                               many of its 64 lanes are still traversing */
   uint32_t tile_particles; /* multiple of 64 in [64, 65536], default 16384: particles per work tile
-                              of the persistent kernel; read when a batch or server is created */
-  uint32_t groups_per_cu;  /* 1..32, default 8: workgroups (256 lanes) per compute unit of the
-                              persistent launches (batches and server steps) */
+                              of the persistent kernel (waves take at most a quarter of it at a
+                              time); read when a batch or server is created */
+  uint32_t groups_per_cu;  /* 1..32, default 8: cap, in workgroups (256 lanes) per compute unit, of
+                              the persistent launches (batches and server steps); never more are
+                              launched than can be resident at once (at most four) or have work */
   uint32_t plain_groups_per_cu; /* 0..32, default 4 (0 selects it): cap, in workgroups per compute
                               unit, of the grid of tpmc_trace; the grid also keeps at least four
                               particles per lane, so small queries get fewer workgroups */

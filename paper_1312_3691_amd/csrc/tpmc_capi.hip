@@ -89,10 +89,13 @@ struct Layout {
   ResultDev* res;
   long long* scal;
   long long* tally;
-  uint64_t* tiles;       // batch: tiles per query
-  unsigned long long* next;  // batch: claim counter per query
+  unsigned long long* next;  // batch: claim counters
+  uint64_t counters;         // their number (whole 256-byte lines: at least 32)
   float* planes[6];
-  uint64_t bytes;
+  ScalCopies copies;         // of the scalar blocks; none where the workspace has no room for them
+  uint64_t copy_words;
+  uint64_t need;             // bytes without the copies
+  uint64_t bytes;            // bytes with them
 };
 
 struct tpmc_particles_s {
@@ -114,12 +117,11 @@ struct tpmc_batch_s {
   tpmc_mesh mesh;
   uint32_t nq;
   std::vector<QueryDev> hq;
-  std::vector<uint64_t> tiles;
   Layout lay;
-  uint64_t total_tiles;
   uint64_t tally_words;
   TallyMode mode;
-  int grid;
+  int n_cu, groups_per_cu;
+  uint64_t total_particles;
   uint32_t tile;
   uint32_t refill;
   hipGraphExec_t exec;
@@ -386,8 +388,26 @@ static tpmc_status make_queries(tpmc_mesh m, const tpmc_query* q, uint32_t nq, s
 // ---------------------------------------------------------------------------
 static uint64_t align256(uint64_t v) { return (v + 255) & ~255ull; }
 
-// Lays out [queries | results | scalar blocks | tallies | tiles | claim counters | 6 planes].
-static void layout(std::vector<QueryDev>& hq, uint64_t nt, uint64_t n_planes, bool batch, uint8_t* base, Layout& L) {
+static uint64_t total_particles(const std::vector<QueryDev>& hq) {
+  uint64_t n = 0;
+  for (const auto& q : hq) n += q.N;
+  return n;
+}
+
+// Copies (log2) of each of nq scalar blocks of a launch over `waves` waves: one
+// per 64 waves that add into a block (64 adds into one address take 0.8 us),
+// none for fewer.
+static uint32_t copies_log2(uint64_t nq, uint64_t waves) {
+  uint32_t l = 0;
+  while (l < 6 && (nq * 64ull << l) < waves) ++l;
+  return l;
+}
+constexpr uint64_t kMostWaves = 4096;  // resident waves of a launch on 256 compute units
+
+// Lays out [queries | results | scalar blocks | tallies | claim counters | 6 planes | copies of the scalar blocks]
+// in ws_bytes at base.
+static void layout(std::vector<QueryDev>& hq, uint64_t nt, uint64_t n_planes, bool batch, uint8_t* base,
+                   uint64_t ws_bytes, Layout& L) {
   const uint64_t nq = hq.size();
   uint64_t off = 0;
   auto take = [&](uint64_t bytes) {
@@ -405,24 +425,26 @@ static void layout(std::vector<QueryDev>& hq, uint64_t nt, uint64_t n_planes, bo
     if (hq[i].per_tri) words += nt * 7;
   }
   const uint64_t o_t = take(words * sizeof(long long));
-  const uint64_t o_te = take(batch ? nq * sizeof(uint64_t) : 0);
   const uint64_t o_c = take(batch ? nq * sizeof(uint64_t) : 0);
   uint64_t o_p[6];
   for (int k = 0; k < 6; ++k) o_p[k] = take(n_planes * sizeof(float));
+  L.need = off;
+  const uint32_t cl = copies_log2(nq, std::min<uint64_t>(kMostWaves, total_particles(hq) / 64));
+  L.copy_words = cl ? (nq << cl) * kScalStride : 0;
+  const uint64_t o_sc = take(L.copy_words * sizeof(long long));
   L.bytes = off;
+  L.copies = ScalCopies{reinterpret_cast<long long*>(base + o_sc), cl};
+  if (cl == 0 || ws_bytes < L.bytes) {
+    L.copies = ScalCopies{nullptr, 0};
+    L.copy_words = 0;
+  }
   L.qs = reinterpret_cast<QueryDev*>(base + o_q);
   L.res = reinterpret_cast<ResultDev*>(base + o_r);
   L.scal = reinterpret_cast<long long*>(base + o_s);
   L.tally = reinterpret_cast<long long*>(base + o_t);
-  L.tiles = reinterpret_cast<uint64_t*>(base + o_te);
   L.next = reinterpret_cast<unsigned long long*>(base + o_c);
+  L.counters = batch ? align256(nq * sizeof(uint64_t)) / sizeof(uint64_t) : 0;
   for (int k = 0; k < 6; ++k) L.planes[k] = reinterpret_cast<float*>(base + o_p[k]);
-}
-
-static uint64_t total_particles(const std::vector<QueryDev>& hq) {
-  uint64_t n = 0;
-  for (const auto& q : hq) n += q.N;
-  return n;
 }
 
 static TallyMode plain_mode(const QueryDev& q, uint64_t nt) {
@@ -637,7 +659,7 @@ extern "C" tpmc_status tpmc_workspace_bytes(tpmc_ctx ctx, tpmc_mesh m, const tpm
   tpmc_status s = make_queries(m, q, nq, hq);
   if (s != TPMC_OK) return s;
   Layout L;
-  layout(hq, m->nt, total_particles(hq), false, nullptr, L);
+  layout(hq, m->nt, total_particles(hq), false, nullptr, 0, L);
   *bytes = L.bytes;
   return TPMC_OK;
 }
@@ -669,8 +691,8 @@ extern "C" tpmc_status tpmc_seed(tpmc_ctx ctx, tpmc_mesh m, const tpmc_query* q,
     hq.p_offset = off;
     off += hq.N;
   }
-  layout(p->hq, m->nt, p->n_total, false, static_cast<uint8_t*>(ws), p->lay);
-  s = check_ws(ws, ws_bytes, p->lay.bytes);
+  layout(p->hq, m->nt, p->n_total, false, static_cast<uint8_t*>(ws), ws_bytes, p->lay);
+  s = check_ws(ws, ws_bytes, p->lay.need);
   if (s != TPMC_OK) {
     delete p;
     return s;
@@ -684,8 +706,8 @@ extern "C" tpmc_status tpmc_seed(tpmc_ctx ctx, tpmc_mesh m, const tpmc_query* q,
   }
   uint64_t words = 0;
   for (const auto& hq : p->hq) words += hq.per_tri ? m->nt * 7 : 0;
-  zero_i64(p->lay.scal, (uint64_t)nq * kScalarSlots, ctx->stream);
-  zero_i64(p->lay.tally, words, ctx->stream);
+  clear_ranges({{p->lay.scal, p->lay.tally, p->lay.copies.base, nullptr},
+                {(uint64_t)nq * kScalarSlots, words, p->lay.copy_words, 0}}, ctx->stream);
   for (uint32_t i = 0; i < nq; ++i) {
     const QueryDev& hq = p->hq[i];
     float* const x[3] = {p->lay.planes[0] + hq.p_offset, p->lay.planes[1] + hq.p_offset,
@@ -742,6 +764,9 @@ extern "C" tpmc_status tpmc_trace_ex(tpmc_ctx ctx, tpmc_mesh m, tpmc_particles p
     a.n = hq.N;
     a.tally = hq.per_tri ? p->lay.tally + hq.tally_offset : nullptr;
     a.scal = p->lay.scal + hq.scalar_offset;
+    const ScalCopies& sc = p->lay.copies;
+    a.copies = sc.base ? sc.base + ((uint64_t)i << sc.log2) * kScalStride : nullptr;
+    a.copy_mask = (1u << sc.log2) - 1u;
     a.first_tri = dev_first_tri ? dev_first_tri + hq.p_offset : nullptr;
     a.counters = reinterpret_cast<unsigned long long*>(dev_counters);
     a.nt = (uint32_t)m->nt;
@@ -794,7 +819,7 @@ static tpmc_status finalize_results(tpmc_ctx ctx, const Layout& L, uint32_t nq, 
                                     double A_ref, tpmc_result* out) {
   const double xr = ref_point ? ref_point[0] : 0.0, yr = ref_point ? ref_point[1] : 0.0,
                zr = ref_point ? ref_point[2] : 0.0;
-  launch_finalize(L.qs, nullptr, L.scal, nq, xr, yr, zr, A_ref, L.res, ctx->stream);
+  launch_finalize(L.qs, nullptr, L.scal, L.copies, nq, xr, yr, zr, A_ref, L.res, ctx->stream);
   HIP_CHECK_LAUNCH("finalize");
   std::vector<ResultDev> hr(nq);
   HIP_TRY(hipMemcpyAsync(hr.data(), L.res, nq * sizeof(ResultDev), hipMemcpyDeviceToHost, ctx->stream));
@@ -858,13 +883,11 @@ extern "C" void tpmc_destroy_tally(tpmc_tally t) { delete t; }
 // batched path
 // ---------------------------------------------------------------------------
 
-static tpmc_status batch_prepare(tpmc_mesh m, const tpmc_query* q, uint32_t nq, uint32_t tile,
-                                 std::vector<QueryDev>& hq, std::vector<uint64_t>& tiles, Layout& L, uint8_t* base) {
+static tpmc_status batch_prepare(tpmc_mesh m, const tpmc_query* q, uint32_t nq, std::vector<QueryDev>& hq, Layout& L,
+                                 uint8_t* base, uint64_t ws_bytes) {
   tpmc_status s = make_queries(m, q, nq, hq);
   if (s != TPMC_OK) return s;
-  tiles.resize(nq);
-  for (uint32_t i = 0; i < nq; ++i) tiles[i] = (hq[i].N + tile - 1) / tile;
-  layout(hq, m->nt, 0, true, base, L);
+  layout(hq, m->nt, 0, true, base, ws_bytes, L);
   return TPMC_OK;
 }
 
@@ -872,28 +895,24 @@ extern "C" tpmc_status tpmc_batch_workspace_bytes(tpmc_ctx ctx, tpmc_mesh m, con
                                                   uint64_t* bytes) {
   if (!ctx || !m || !bytes) return fail(TPMC_E_INVALID, "ctx, mesh and bytes must not be NULL");
   std::vector<QueryDev> hq;
-  std::vector<uint64_t> te;
   Layout L;
-  tpmc_status s = batch_prepare(m, q, nq, ctx->tune.tile_particles, hq, te, L, nullptr);
+  tpmc_status s = batch_prepare(m, q, nq, hq, L, nullptr, 0);
   if (s != TPMC_OK) return s;
   *bytes = L.bytes;
   return TPMC_OK;
 }
 
 // Fills b for the queries q on mesh m with its workspace at ws (ws_bytes) and
-// uploads the query table and tile counts (synchronises).  Allocates nothing.
+// uploads the query table (synchronises).  Allocates nothing.
 static tpmc_status batch_init(tpmc_ctx ctx, tpmc_mesh m, const tpmc_query* q, uint32_t nq, void* ws,
                               uint64_t ws_bytes, tpmc_batch_s* b) {
-  tpmc_status s = batch_prepare(m, q, nq, ctx->tune.tile_particles, b->hq, b->tiles, b->lay,
-                                static_cast<uint8_t*>(ws));
-  if (s == TPMC_OK) s = check_ws(ws, ws_bytes, b->lay.bytes);
+  tpmc_status s = batch_prepare(m, q, nq, b->hq, b->lay, static_cast<uint8_t*>(ws), ws_bytes);
+  if (s == TPMC_OK) s = check_ws(ws, ws_bytes, b->lay.need);
   if (s != TPMC_OK) return s;
   b->ctx = ctx;
   b->device = ctx->device;
   b->mesh = m;
   b->nq = nq;
-  b->total_tiles = 0;
-  for (uint64_t t : b->tiles) b->total_tiles += t;
   b->tally_words = 0;
   bool any_tri = false, all_tri = true;
   for (const auto& hq : b->hq) {
@@ -906,7 +925,9 @@ static tpmc_status batch_init(tpmc_ctx ctx, tpmc_mesh m, const tpmc_query* q, ui
   b->mode = !any_tri ? kTallyTotals
                      : (m->nt <= (uint64_t)kLaneTallyMaxTris ? kTallyLane
                                                             : (m->nt <= (uint64_t)kLdsTallyMaxTris ? kTallyLds : kTallyGlobal));
-  b->grid = ctx->n_cu * (int)ctx->tune.groups_per_cu;
+  b->n_cu = ctx->n_cu;
+  b->groups_per_cu = (int)ctx->tune.groups_per_cu;
+  b->total_particles = total_particles(b->hq);
   b->tile = ctx->tune.tile_particles;
   b->refill = ctx->tune.refill_lanes;
   b->exec = nullptr;
@@ -914,9 +935,6 @@ static tpmc_status batch_init(tpmc_ctx ctx, tpmc_mesh m, const tpmc_query* q, ui
   hipError_t e = hipSetDevice(ctx->device);
   if (e == hipSuccess)
     e = hipMemcpyAsync(b->lay.qs, b->hq.data(), nq * sizeof(QueryDev), hipMemcpyHostToDevice, ctx->stream);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(b->lay.tiles, b->tiles.data(), nq * sizeof(uint64_t), hipMemcpyHostToDevice,
-                       ctx->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
   if (e != hipSuccess) return fail(TPMC_E_DEVICE, "batch upload: %s", hipGetErrorString(e));
   return TPMC_OK;
@@ -940,23 +958,23 @@ extern "C" tpmc_status tpmc_batch_create(tpmc_ctx ctx, tpmc_mesh m, const tpmc_q
 
 static void batch_enqueue(tpmc_batch b, hipStream_t st) {
   tpmc_mesh m = b->mesh;
-  zero_i64(reinterpret_cast<long long*>(b->lay.next), b->nq, st);
-  zero_i64(b->lay.scal, (uint64_t)b->nq * kScalarSlots, st);
-  zero_i64(b->lay.tally, b->tally_words, st);
+  clear_ranges({{reinterpret_cast<long long*>(b->lay.next), b->lay.scal, b->lay.tally, b->lay.copies.base},
+                {b->lay.counters, (uint64_t)b->nq * kScalarSlots, b->tally_words, b->lay.copy_words}}, st);
   BatchArgs a{};
   a.qs = b->lay.qs;
   a.entry_query = nullptr;
   a.entry_tile0 = nullptr;
-  a.entry_tiles = b->lay.tiles;
+  a.entry_tiles = nullptr;
   a.entry_next = b->lay.next;
   a.tally_base = b->lay.tally;
   a.scal_base = b->lay.scal;
+  a.copies = b->lay.copies;
   a.n_entries = b->nq;
   a.refill = b->refill;
   a.tile = b->tile;
   a.lds_tris = b->mode == kTallyLds ? (uint32_t)m->nt : 0u;
   a.wave_totals = b->mode == kTallyTotals ? 1u : 0u;
-  launch_batch(a, m->stack_slots, b->mode, b->grid, st);
+  launch_batch(a, m->stack_slots, b->mode, b->total_particles, true, b->lay.counters, b->n_cu, b->groups_per_cu, st);
   if (b->mode != kTallyTotals) launch_reduce_batch(b->lay.qs, b->nq, b->lay.tally, b->lay.scal, (uint32_t)m->nt, st);
 }
 
@@ -1026,13 +1044,12 @@ extern "C" tpmc_status tpmc_batch_run_noalloc(tpmc_ctx ctx, tpmc_mesh m, const t
   if (!ws) return fail(TPMC_E_DEVICE, "no static workspace address for device %d", ctx->device);
   tpmc_batch_s b;
   std::vector<QueryDev> hq;
-  std::vector<uint64_t> te;
   Layout L;
-  tpmc_status s = batch_prepare(m, q, nq, ctx->tune.tile_particles, hq, te, L, nullptr);
+  tpmc_status s = batch_prepare(m, q, nq, hq, L, nullptr, 0);
   if (s != TPMC_OK) return s;
-  if (L.bytes > kScratchBytes)
+  if (L.need > kScratchBytes)
     return fail(TPMC_E_WORKSPACE, "these queries need %llu bytes of workspace; the static workspace holds %llu",
-                (unsigned long long)L.bytes, (unsigned long long)kScratchBytes);
+                (unsigned long long)L.need, (unsigned long long)kScratchBytes);
   s = batch_init(ctx, m, q, nq, ws, kScratchBytes, &b);
   if (s != TPMC_OK) return s;
   batch_enqueue(&b, ctx->stream);  // zeroes the claim counters, scalars and tallies it uses
@@ -1062,6 +1079,7 @@ struct tpmc_server_s {
   uint8_t* entries;      // step entries: tile0 [n] u64, tiles [n] u64, slot [n] u32 (packed for n)
   uint8_t* admits;       // admission staging: [max_slots] AdmitRec
   uint32_t* r_idx;       // [2][max_slots] slots whose results are collected
+  ScalCopies copies;     // of the slots' scalar blocks (none in a workspace without room for them)
   unsigned long long* e_next;
   std::vector<QueryDev> hq;
   std::vector<tpmc_mesh> mesh_of;
@@ -1080,8 +1098,9 @@ struct tpmc_server_s {
   bool coll_pending[2] = {false, false};
 };
 
-static void server_layout(uint32_t max_slots, uint64_t tally_words, uint8_t* base, tpmc_server_s* s,
-                          uint64_t* bytes) {
+// *need: the bytes a server cannot do without; *bytes: with the copies of its scalar blocks.
+static void server_layout(uint32_t max_slots, uint64_t tally_words, uint8_t* base, uint64_t ws_bytes,
+                          tpmc_server_s* s, uint64_t* need, uint64_t* bytes) {
   uint64_t off = 0;
   auto take = [&](uint64_t b) {
     const uint64_t o = off;
@@ -1092,8 +1111,12 @@ static void server_layout(uint32_t max_slots, uint64_t tally_words, uint8_t* bas
                  os = take((uint64_t)max_slots * kScalarSlots * 8), ot = take(tally_words * 8),
                  oe = take(max_slots * 20ull), oa = take(max_slots * sizeof(AdmitRec)),
                  ori = take(2ull * max_slots * 4), oc = take(max_slots * 8ull);
+  *need = off;
+  const uint32_t cl = copies_log2(max_slots, kMostWaves);
+  const uint64_t osc = take(((uint64_t)max_slots << cl) * kScalStride * 8);
   *bytes = off;
   if (!s) return;
+  s->copies = cl == 0 || ws_bytes < off ? ScalCopies{nullptr, 0} : ScalCopies{reinterpret_cast<long long*>(base + osc), cl};
   s->qs = reinterpret_cast<QueryDev*>(base + oq);
   s->res = reinterpret_cast<ResultDev*>(base + orr);
   s->scal = reinterpret_cast<long long*>(base + os);
@@ -1131,7 +1154,8 @@ static tpmc_status server_upload(tpmc_server s, void* dst, const void* src, uint
 
 extern "C" tpmc_status tpmc_server_workspace_bytes(uint32_t max_slots, uint64_t tally_words, uint64_t* bytes) {
   if (!bytes || max_slots == 0) return fail(TPMC_E_INVALID, "need max_slots >= 1 and an output");
-  server_layout(max_slots, tally_words, nullptr, nullptr, bytes);
+  uint64_t need = 0;
+  server_layout(max_slots, tally_words, nullptr, 0, nullptr, &need, bytes);
   return TPMC_OK;
 }
 
@@ -1139,8 +1163,8 @@ extern "C" tpmc_status tpmc_server_create(tpmc_ctx ctx, uint32_t max_slots, uint
                                           uint64_t ws_bytes, tpmc_server* out) {
   if (!ctx || !out || max_slots == 0) return fail(TPMC_E_INVALID, "ctx, out and max_slots >= 1 required");
   *out = nullptr;
-  uint64_t need = 0;
-  server_layout(max_slots, tally_words, nullptr, nullptr, &need);
+  uint64_t need = 0, bytes = 0;
+  server_layout(max_slots, tally_words, nullptr, 0, nullptr, &need, &bytes);
   tpmc_status st = check_ws(ws, ws_bytes, need);
   if (st != TPMC_OK) return st;
   tpmc_server s = new (std::nothrow) tpmc_server_s;
@@ -1150,7 +1174,7 @@ extern "C" tpmc_status tpmc_server_create(tpmc_ctx ctx, uint32_t max_slots, uint
   s->max_slots = max_slots;
   s->tally_words = tally_words;
   s->tile = ctx->tune.tile_particles;
-  server_layout(max_slots, tally_words, static_cast<uint8_t*>(ws), s, &need);
+  server_layout(max_slots, tally_words, static_cast<uint8_t*>(ws), ws_bytes, s, &need, &bytes);
   s->hq.assign(max_slots, QueryDev{});
   s->mesh_of.assign(max_slots, nullptr);
   s->used.assign(max_slots, 0);
@@ -1213,7 +1237,8 @@ extern "C" tpmc_status tpmc_server_admit_many(tpmc_server s, uint32_t n, const u
   }
   tpmc_status st = server_upload(s, s->admits, rec.data(), n * sizeof(AdmitRec));
   if (st != TPMC_OK) return st;
-  launch_admit(reinterpret_cast<const AdmitRec*>(s->admits), n, max_words, s->qs, s->scal, s->tally, s->ctx->stream);
+  launch_admit(reinterpret_cast<const AdmitRec*>(s->admits), n, max_words, s->qs, s->scal, s->copies, s->tally,
+               s->ctx->stream);
   HIP_CHECK_LAUNCH("admit");
   return TPMC_OK;
 }
@@ -1280,7 +1305,8 @@ extern "C" tpmc_status tpmc_server_step(tpmc_server s, const uint32_t* slots, co
   }
   tpmc_status ust = server_upload(s, s->entries, pk.data(), pk.size());
   if (ust != TPMC_OK) return ust;
-  zero_i64(reinterpret_cast<long long*>(s->e_next), n, st);
+  const uint64_t counters = align256(s->max_slots * 8ull) / 8;  // words of the region at e_next
+  zero_i64(reinterpret_cast<long long*>(s->e_next), std::min<uint64_t>(counters, std::max(n, 16u)), st);
   BatchArgs a{};
   a.qs = s->qs;
   a.entry_tile0 = reinterpret_cast<const uint64_t*>(s->entries);
@@ -1289,6 +1315,7 @@ extern "C" tpmc_status tpmc_server_step(tpmc_server s, const uint32_t* slots, co
   a.entry_next = s->e_next;
   a.tally_base = s->tally;
   a.scal_base = s->scal;
+  a.copies = s->copies;
   a.n_entries = n;
   a.refill = s->ctx->tune.refill_lanes;
   a.tile = s->tile;
@@ -1298,7 +1325,8 @@ extern "C" tpmc_status tpmc_server_step(tpmc_server s, const uint32_t* slots, co
   a.lds_tris = mode == kTallyAuto ? lds_tris : 0u;
   a.wave_totals = any_totals ? 1u : 0u;
   for (int k = 0; k < 9; ++k) a.xcd_start[k] = xs[k];
-  launch_batch(a, stack, mode, s->ctx->n_cu * (int)s->ctx->tune.groups_per_cu, st);
+  launch_batch(a, stack, mode, acc * s->tile, false, std::max<uint64_t>(n, std::min<uint64_t>(counters, 16)),
+               s->ctx->n_cu, (int)s->ctx->tune.groups_per_cu, st);
   HIP_CHECK_LAUNCH("server step");
   return TPMC_OK;
 }
@@ -1326,7 +1354,7 @@ extern "C" tpmc_status tpmc_server_collect(tpmc_server s, const uint32_t* slots,
   launch_reduce_slots(s->qs, idx, n, s->tally, s->scal, max_nt, st);
   const double xr = ref_point ? ref_point[0] : 0.0, yr = ref_point ? ref_point[1] : 0.0,
                zr = ref_point ? ref_point[2] : 0.0;
-  launch_finalize(s->qs, idx, s->scal, n, xr, yr, zr, A_ref, res, st);
+  launch_finalize(s->qs, idx, s->scal, s->copies, n, xr, yr, zr, A_ref, res, st);
   HIP_CHECK_LAUNCH("server collect");
   HIP_TRY(hipMemcpyAsync(s->res_host + (uint64_t)b * s->max_slots, res, n * sizeof(ResultDev), hipMemcpyDeviceToHost,
                          st));

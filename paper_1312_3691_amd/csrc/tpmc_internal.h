@@ -10,7 +10,8 @@ constexpr int kWaves = kBlock / 64;
 constexpr int kMaxReflections = 64;
 constexpr int kLdsTallyMaxTris = 512;  // per-workgroup LDS tallies up to this mesh size
 constexpr int kLaneTallyMaxTris = 2;   // per-lane LDS tallies for tiny meshes
-constexpr int kScalarSlots = 21;       // int64 per query, see ScalarSlot
+constexpr int kScalarSlots = 20;       // int64 per query, see ScalarSlot
+constexpr int kScalStride = 32;        // int64 from one copy of a scalar block to the next (whole cache lines)
 
 // Per-query int64 block.  D is the momentum one particle gives the body along
 // the free stream (sum over its hits of (w - w').U); D and D^2 are quantised
@@ -21,8 +22,7 @@ enum ScalarSlot {
   kSE = 15, kSE2 = 16,  // per-particle energy E = sum over hits of |w|^2 - |w'|^2, and E^2
   kTrCap = 17,          // diffuse re-emissions whose temperature the kernel's bound limited
   kGuard = 18,          // ray segments ended by the traversal step bound (a damaged tree)
-  kPreculled = 19,      // particles the seeding estimate showed to miss the root's boxes (batched kernel)
-  kPrecullOff = 20      // nonzero once the batched kernel has switched the estimate off for this query
+  kPreculled = 19       // particles the seeding estimate showed to miss the root's boxes (batched kernel)
 };
 
 // Phase probe of the batched kernel (compiled in only with TPMC_PHASE_PROBE=1):

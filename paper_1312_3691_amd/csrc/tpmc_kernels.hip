@@ -5,8 +5,11 @@
 //   reduce/finalize a10    exact integer reduction, force / moment / C_D in FP64
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "tpmc_device.hpp"
 #include "tpmc_launch.h"
+#include "tpmc_units.hpp"
 
 #ifndef TPMC_PHASE_PROBE
 #define TPMC_PHASE_PROBE 0
@@ -26,6 +29,14 @@ namespace {
 __global__ void zero_i64_kernel(long long* __restrict__ p, uint64_t n) {
   for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
     p[i] = 0;
+}
+
+// Several ranges in one launch (the work of a launch costs less than the launch).
+__global__ void clear_kernel(ClearRanges r) {
+  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+#pragma unroll
+  for (int k = 0; k < kClearRanges; ++k)
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < r.n[k]; i += stride) r.p[k][i] = 0;
 }
 
 __global__ void zero_u32_kernel(uint32_t* __restrict__ p, uint64_t n) {
@@ -658,7 +669,7 @@ __global__ __launch_bounds__(kBlock) void trace_kernel(TraceArgs a) {
     if (L.live && seg_traversing(s))
       trav_step<STACK, COUNT>(a.nodes, a.tris, a.orig, r, L.prev, s, stk, A.nodes, A.tests);
   }
-  flush_acc(A, a.scal, MODE == kTallyTotals);
+  flush_acc(A, a.copies ? a.copies + (uint64_t)(blockIdx.x & a.copy_mask) * kScalStride : a.scal, MODE == kTallyTotals);
   if (MODE == kTallyLane) flush_lane_tally(lt, a.tally, a.nt);
   if (COUNT) {
     const long long nn = wave_sum((long long)A.nodes), nt2 = wave_sum((long long)A.tests);
@@ -675,12 +686,11 @@ __global__ __launch_bounds__(kBlock) void trace_kernel(TraceArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// a11: persistent batched kernel.  A workgroup claims tiles of one work entry
-// (a query, or a range of its tiles) from that entry's counter until the entry
-// is exhausted, then moves to the next entry with work left; its four waves
-// share each tile, claiming 64 particles at a time from a workgroup counter in
-// LDS.  A wave seeds its 64 particles with every lane active (the FP64 seeding
-// is the costliest per-particle step) into a wave-private LDS queue; the
+// a11: persistent batched kernel.  A wave claims units of one part of a work
+// entry (a query, or a range of its tiles) until the part is used up, then
+// moves to another part with work left.  It draws 64 particles at a time from
+// its unit and seeds them with every lane active (the FP64 seeding is the
+// costliest per-particle step) into a wave-private LDS queue; the
 // traversal advances one BVH step per iteration as in the plain path, and when
 // fewer than a.refill lanes are still traversing, the lanes whose segment has
 // ended are served together and lanes whose particle retired take the next
@@ -697,36 +707,103 @@ __global__ __launch_bounds__(kBlock) void trace_kernel(TraceArgs a) {
 template <int STACK, int MODE>
 constexpr bool kPrecullInstance = STACK <= 32;
 
-// Work is claimed per wave in units of a quarter tile (a whole tile when the
-// tile is not a multiple of 256 particles): a wave's lanes draw particles
-// from its own unit, and when the unit runs out while lanes are still busy
-// the wave goes on with another unit of the same entry instead of draining
-// (lanes in flight keep their absolute particle ids), so waves drain only
-// when their entry is used up.  Where no tally state is shared by the
-// workgroup's waves (global atomics, per-lane LDS tallies, the waves' own
-// totals) each wave also chooses its entries alone and never waits for the
-// others; with workgroup LDS tallies the workgroup chooses the entry together
-// and its waves meet at a barrier only when they leave it (the tallies are
-// flushed then).
+// Work is claimed per wave in units of whole 64-particle batches (tpmc_units.hpp): a
+// wave's lanes draw particles from its own unit, and when the unit runs out
+// while lanes are still busy the wave goes on with another unit of the same
+// part instead of draining (lanes in flight keep their absolute particle ids),
+// so waves drain only when their part is used up.  Where no tally state is
+// shared by the workgroup's waves (global atomics, per-lane LDS tallies, the
+// waves' own totals) each wave also chooses its parts alone and never waits
+// for the others; with workgroup LDS tallies the workgroup chooses the part
+// together and its waves meet at a barrier only when they leave it (the
+// tallies are flushed then).
 template <int MODE>
 constexpr bool kWaveEntries = MODE == kTallyGlobal || MODE == kTallyLane || MODE == kTallyTotals;
 
-// Claim the next tile (or quarter tile) of the entry list from `scan` on:
-// the current entry first, then the following ones (bounded scan).  Returns
-// the entry, or kNoEntry when every entry is used up; t gets the unit's index.
 constexpr uint32_t kNoEntry = 0xFFFFFFFFu;
 
-__device__ __forceinline__ uint32_t claim_unit(const BatchArgs& a, uint32_t& scan, uint32_t units_per_tile,
-                                               unsigned long long& t) {
-  for (uint32_t k = 0; k < a.n_entries; ++k) {
-    const uint64_t cap = a.entry_tiles[scan] * units_per_tile;
-    if (__hip_atomic_load(&a.entry_next[scan], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < cap) {
-      t = atomicAdd(&a.entry_next[scan], 1ull);
-      if (t < cap) return scan;
+// The cut of a part into units (tpmc_units.hpp).
+__device__ __forceinline__ UnitPlan unit_plan(const BatchArgs& a, uint32_t part) {
+  const uint32_t j = part >> a.sub_log2, i = part & ((1u << a.sub_log2) - 1u);
+  const uint64_t N = a.qs[a.entry_query ? a.entry_query[j] : j].N;
+  const uint64_t e0 = a.entry_tile0 ? a.entry_tile0[j] * a.tile : 0ull;
+  uint64_t e1 = a.entry_tiles ? e0 + a.entry_tiles[j] * a.tile : N;
+  if (e1 > N) e1 = N;
+  const uint64_t ns = (uint64_t)(a.start_div + (part < a.start_rem ? 1u : 0u)) * (uint32_t)kWaves;
+  return unit_plan_of(e0, e1 > e0 ? e1 - e0 : 0ull, a.sub_log2, i, ns, a.share_log2, a.unit_cap_log2);
+}
+
+// Claim a counted unit of the part (one atomic by lane 0; uniform result).
+__device__ __forceinline__ bool claim_counted(const BatchArgs& a, uint32_t part, const UnitPlan& p, uint64_t& b,
+                                              uint64_t& e) {
+  if (p.ns_end >= p.n) return false;  // starting units only
+  unsigned long long t = 0;
+  if ((threadIdx.x & 63) == 0) t = atomicAdd(&a.entry_next[part], 1ull);
+  t = (unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)t) |
+      ((unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(t >> 32)) << 32);
+  const bool ok = counted_unit(p, t, b, e);
+  b += p.lo;
+  e += p.lo;
+  return ok;
+}
+
+// Find a part with counted units left, from part `scan` on, and claim one: 64
+// parts are looked at per step, one per lane (called by a whole wave; uniform
+// result, kNoEntry when there is none).  A failed claim on a part means that
+// it was used up meanwhile.  Where every part has waves that started on it
+// (they stay until it is used up), its last small units are left to them:
+// taking up another query, draining and flushing cost more than such a unit.
+constexpr uint64_t kJoinMin = 256;
+__device__ __forceinline__ uint32_t claim_any(const BatchArgs& a, uint32_t scan, uint64_t& b, uint64_t& e) {
+  const uint32_t parts = a.n_entries << a.sub_log2, lane = threadIdx.x & 63u;
+  for (uint32_t k = 0; k < parts; k += 64u) {
+    uint32_t part = scan + k + lane;
+    if (part >= parts) part -= parts;
+    bool has = false;
+    if (k + lane < parts) {
+      const UnitPlan p = unit_plan(a, part);
+      uint64_t x, y;
+      has = counted_unit(p, __hip_atomic_load(&a.entry_next[part], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), x, y);
+      has = has && (a.start_div == 0u || y - x >= kJoinMin);
     }
-    scan = scan + 1 == a.n_entries ? 0u : scan + 1;
+    uint64_t m = ballot(has);
+    while (m != 0ull) {
+      uint32_t c = scan + k + (uint32_t)__builtin_ctzll(m);
+      m &= m - 1ull;
+      if (c >= parts) c -= parts;
+      if (claim_counted(a, c, unit_plan(a, c), b, e)) return c;
+    }
   }
   return kNoEntry;
+}
+
+// The part a workgroup starts on.  Workgroups are ordered by XCD, then (where
+// the grid fills whole rounds of them) by compute unit, and the parts dealt to
+// them in that order, so that a compute unit's waves work on one query or few:
+// its rows of the latitude table (10 KB in reach of a query) stay in the
+// 32 KB L1.  (The hardware deals workgroups to the XCDs in turn, and within
+// an XCD to its compute units in turn; only speed depends on it.)
+__device__ __forceinline__ void start_part(const BatchArgs& a, uint32_t& part, uint32_t& rank) {
+  const uint32_t G = gridDim.x, x = blockIdx.x & 7u, y = blockIdx.x >> 3;
+  const uint32_t rem8 = G & 7u, cus = a.xcd_cus;
+  uint32_t i = x * (G >> 3) + (x < rem8 ? x : rem8);
+  if (rem8 == 0u && (G >> 3) % cus == 0u) i += (y % cus) * ((G >> 3) / cus) + y / cus;
+  else i += y;
+  const uint32_t more = a.start_rem * (a.start_div + 1u);  // the first start_rem parts have one workgroup more
+  if (i < more) {
+    part = i / (a.start_div + 1u);
+    rank = i % (a.start_div + 1u);
+  } else {  // start_div > 0 here
+    part = a.start_rem + (i - more) / a.start_div;
+    rank = (i - more) % a.start_div;
+  }
+}
+
+// Where the workgroup's waves add a query's sums: the query's block, or one of
+// its copies (ScalCopies).
+__device__ __forceinline__ long long* scal_block(const BatchArgs& a, uint32_t query, const QueryDev& q) {
+  if (a.copies.base == nullptr) return a.scal_base + q.scalar_offset;
+  return a.copies.base + (((uint64_t)query << a.copies.log2) + (blockIdx.x & ((1u << a.copies.log2) - 1u))) * kScalStride;
 }
 
 __device__ __forceinline__ uint64_t uniform_u64(uint64_t v) {
@@ -752,14 +829,18 @@ __global__ __launch_bounds__(kBlock) PROBE(__attribute__((amdgpu_waves_per_eu(ST
   extern __shared__ unsigned long long lt[];  // tallies in LDS, sized at launch (tally_lds_bytes)
   // per-wave totals [c][wave]: the start of lt, or after the per-triangle area in the mixed mode
   unsigned long long* const wave_tot = MODE == kTallyAuto ? lt + 7u * a.lds_tris : lt;
-  __shared__ unsigned long long tile_sh;
+  __shared__ unsigned long long unit_sh[2];         // wave 0's claimed unit of the workgroup's part
   __shared__ unsigned long long w_next_sh[kWaves];  // each wave's next unclaimed particle
-  __shared__ uint32_t entry_sh;
+  __shared__ uint32_t part_sh;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  uint32_t scan;  // the claiming thread's position in the entry list (thread 0, or each wave's lane 0)
-  {
+  // the part the workgroup starts on, and where its waves look for work
+  uint32_t scan, rank = kNone;  // rank: the workgroup's number among those that start on the part
+  if (a.start_div != 0u || a.start_rem != 0u) {
+    start_part(a, scan, rank);
+  } else {
     const uint32_t x = blockIdx.x & 7u, lo = a.xcd_start[x], hi = a.xcd_start[x + 1];
-    scan = a.xcd_start[8] == 0u ? blockIdx.x % a.n_entries : (hi > lo ? lo + (blockIdx.x >> 3) % (hi - lo) : lo);
+    scan = (hi > lo ? lo + (blockIdx.x >> 3) % (hi - lo) : lo) << a.sub_log2;
+    scan += (blockIdx.x >> 3) & ((1u << a.sub_log2) - 1u);
   }
   uint32_t held = kNone;                     // entry whose partial sums the wave (and workgroup) holds
   Acc A;
@@ -767,11 +848,14 @@ __global__ __launch_bounds__(kBlock) PROBE(__attribute__((amdgpu_waves_per_eu(ST
   PROBE(uint32_t pr = 0u; probe_set<kPrTs>(pr, probe_now()); probe_set<kPrTc>(pr, probe_get(pr, kPrTs));)
   // two-stage seeding, wave-uniform: particles the estimate removed (for the
   // held query), and the estimate's yield so far on it.  A wave that finds
-  // more than 60 % of a query's particles surviving the estimate switches it
-  // off for the query (its kPrecullOff slot, read whenever a wave takes up the query), since the
-  // estimate then costs more than it saves.
+  // more than 60 % of a query's particles surviving the estimate (of at least
+  // one batch) stops using it while it stays on the query, since the estimate
+  // then costs more than it saves.  Every wave finds out for itself: a flag shared by the
+  // launch cost more than the first batches it spared (4096 waves storing to
+  // one word take 125 us, measured).
   uint64_t pre = 0;
   uint32_t pc_seen = 0, pc_kept = 0;
+  auto yields_little = [&]() { return pc_seen >= 64u && 5u * pc_kept > 3u * pc_seen; };
   if (MODE == kTallyLane)
     for (int c = 0; c < 2 * 7; ++c) lt[c * kBlock + threadIdx.x] = 0ull;
   if (MODE == kTallyTotals || (MODE == kTallyAuto && a.wave_totals)) {
@@ -781,37 +865,62 @@ __global__ __launch_bounds__(kBlock) PROBE(__attribute__((amdgpu_waves_per_eu(ST
       wave_tot[threadIdx.x] = 0ull;
     }
   }
-  // claim units per tile (quarter tiles when they stay multiples of 64 particles)
-  const uint32_t units = (a.tile & 255u) == 0u ? 4u : 1u;
   for (;;) {
-    uint32_t j;
-    uint64_t tile;  // claim unit within the entry
-    if (kWave) {
-      uint32_t found = kNone;
-      unsigned long long t = 0;
-      if (lane == 0) found = claim_unit(a, scan, units, t);
-      j = __builtin_amdgcn_readfirstlane(found);  // uniform over the wave
-      tile = uniform_u64(t);
+    uint32_t part;
+    uint64_t p_begin = 0, p_end = 0;  // the wave's unit
+    bool have = true;                 // the wave holds a unit of the part
+    if (rank != kNone) {
+      // the wave's starting unit; where the part is too small to have one for
+      // the workgroup, it has no counted units either
+      const UnitPlan p = unit_plan(a, scan);
+      const uint64_t u = rank * (uint32_t)kWaves + (uint32_t)__builtin_amdgcn_readfirstlane(wave);
+      const uint64_t b = u << p.s_log2, e = (u + 1ull) << p.s_log2;
+      const bool any = kWave ? b < p.n : ((uint64_t)(rank * (uint32_t)kWaves) << p.s_log2) < p.n;
+      part = any ? scan : kNone;
+      have = b < p.n;
+      p_begin = p.lo + b;
+      p_end = p.lo + (e < p.n ? e : p.n);
+      rank = kNone;
+      if (part == kNone) continue;
+    } else if (kWave) {
+      part = claim_any(a, scan, p_begin, p_end);
+      if (part != kNone) scan = part;
     } else {
-      if (threadIdx.x == 0) {  // the workgroup's entry, and wave 0's first unit of it
-        unsigned long long t = 0;
-        entry_sh = claim_unit(a, scan, units, t);
-        tile_sh = t;
+      if (__builtin_amdgcn_readfirstlane(wave) == 0) {  // the workgroup's part, and wave 0's first unit of it
+        part = claim_any(a, scan, p_begin, p_end);
+        if (lane == 0) {
+          part_sh = part;
+          unit_sh[0] = p_begin;
+          unit_sh[1] = p_end;
+        }
       }
       __syncthreads();
-      j = __builtin_amdgcn_readfirstlane(entry_sh);  // uniform over the workgroup
-      tile = uniform_u64(tile_sh);
+      part = __builtin_amdgcn_readfirstlane(part_sh);  // uniform over the workgroup
+      p_begin = uniform_u64(unit_sh[0]);
+      p_end = uniform_u64(unit_sh[1]);
+      if (part != kNone) {
+        scan = part;
+        // the waves share the claimed unit in whole batches
+        const uint64_t each = (((p_end - p_begin + 3ull) >> 2) + 63ull) & ~63ull;
+        const uint64_t first = p_begin + (uint32_t)__builtin_amdgcn_readfirstlane(wave) * each;
+        have = first < p_end;
+        p_begin = first;
+        p_end = first + each < p_end ? first + each : p_end;
+      }
     }
+    const uint32_t j = part == kNone ? kNone : part >> a.sub_log2;
     if (j != held && held != kNone) {
       // leaving the held query: flush its partial sums
-      const QueryDev& qh = a.qs[a.entry_query ? a.entry_query[held] : held];
+      const uint32_t hq = a.entry_query ? a.entry_query[held] : held;
+      const QueryDev& qh = a.qs[hq];
+      long long* const hscal = scal_block(a, hq, qh);
       long long* htally = qh.per_tri ? a.tally_base + qh.tally_offset : nullptr;
       flush_acc<MODE == kTallyTotals || MODE == kTallyAuto>(
-          A, a.scal_base + qh.scalar_offset, MODE == kTallyTotals || (MODE == kTallyAuto && !qh.per_tri), wave_tot);
+          A, hscal, MODE == kTallyTotals || (MODE == kTallyAuto && !qh.per_tri), wave_tot);
       if (MODE == kTallyLane) flush_lane_tally(lt, htally, qh.nt);
       acc_zero(A);
       if (kPre) {
-        if (lane == 0 && pre != 0) atomic_add_i64(a.scal_base + qh.scalar_offset + kPreculled, (long long)pre);
+        if (lane == 0 && pre != 0) atomic_add_i64(hscal + kPreculled, (long long)pre);
         pre = 0;
         pc_seen = pc_kept = 0;
       }
@@ -830,27 +939,6 @@ __global__ __launch_bounds__(kBlock) PROBE(__attribute__((amdgpu_waves_per_eu(ST
       }
       held = j;
     }
-    // particles [p_begin, p_end) of claim unit u of the entry (of its tile u / units);
-    // everything is read again at each claim, so nothing of it stays live across the trace loop
-    auto unit_range = [&](uint64_t u, uint64_t& b, uint64_t& e) {
-      const uint32_t sh = (a.tile & 255u) == 0u ? 2u : 0u;
-      const uint64_t tb = ((a.entry_tile0 ? a.entry_tile0[j] : 0ull) + (u >> sh)) * a.tile;
-      b = tb + (u & ((1u << sh) - 1u)) * (a.tile >> sh);
-      e = b + (a.tile >> sh);
-      if (e > tb + a.tile) e = tb + a.tile;
-      if (e > q.N) e = q.N;
-    };
-    bool have = true;  // the wave holds a unit of entry j
-    // the other waves claim their own first unit of the workgroup's entry (wave number
-    // read into a scalar register, so that the branch and what it sets stay wave-uniform)
-    if (!kWave && __builtin_amdgcn_readfirstlane(wave) != 0) {
-      unsigned long long t = 0;
-      if (lane == 0) t = atomicAdd(&a.entry_next[j], 1ull);
-      tile = uniform_u64(t);
-      have = tile < a.entry_tiles[j] * units;
-    }
-    uint64_t p_begin = 0, p_end = 0;
-    if (have) unit_range(tile, p_begin, p_end);
     if (lane == 0) w_next_sh[wave] = p_begin;  // the next unclaimed particle of the wave's unit
     long long* qtally = q.per_tri ? a.tally_base + q.tally_offset : nullptr;
     const Node* nodes = uniform_ptr(q.nodes);
@@ -873,14 +961,11 @@ __global__ __launch_bounds__(kBlock) PROBE(__attribute__((amdgpu_waves_per_eu(ST
     const uint32_t max_steps = __builtin_amdgcn_readfirstlane(2u * q.nt + 64u);
     uint32_t guard = 0;                // steps since the last service pass (wave-uniform)
     bool exhausted = !have;            // wave-uniform: the unit has no particles left to claim
-    bool dry = !have;                  // wave-uniform: the entry has no units left
+    bool dry = !have;                  // wave-uniform: the part has no units left
     uint32_t q_head = 0, q_count = 0;  // wave-uniform queue state
     uint64_t q_pid0 = 0;               // particle id of queue slot 0
     uint32_t s_head = 0, s_count = 0;  // wave-uniform survivor ring state (two-stage seeding)
-    bool pc_on = true, pc_off_now = false;  // wave-uniform
-    if (kPre)
-      pc_on = __builtin_amdgcn_readfirstlane((uint32_t)__hip_atomic_load(
-                  a.scal_base + q.scalar_offset + kPrecullOff, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 0u;
+    bool pc_on = kPre && !yields_little();  // wave-uniform
     for (;;) {
       uint32_t ntrav = (uint32_t)__popcll(ballot(L.live && seg_traversing(s)));
       if (ntrav < a.refill && ballot(L.live && s.p0 >= 0) != 0ull) {
@@ -919,12 +1004,8 @@ __global__ __launch_bounds__(kBlock) PROBE(__attribute__((amdgpu_waves_per_eu(ST
         const uint64_t dead = ballot(!L.live);
         if (dead != 0ull && exhausted && !dry && q_count == 0 && s_count == 0) {
           // the unit is used up (survivor ring and queue empty, so no offset refers to it):
-          // go on with the entry's next unit while the other lanes are still busy
-          unsigned long long t = 0;
-          if (lane == 0) t = atomicAdd(&a.entry_next[j], 1ull);
-          t = uniform_u64(t);
-          if (t < a.entry_tiles[j] * units) {
-            unit_range(t, p_begin, p_end);
+          // go on with the part's next unit while the other lanes are still busy
+          if (claim_counted(a, part, unit_plan(a, part), p_begin, p_end)) {
             if (lane == 0) w_next_sh[wave] = p_begin;
             exhausted = false;
             PROBE(probe_add<kPrClaims>(pr, 1u);)
@@ -954,10 +1035,7 @@ __global__ __launch_bounds__(kBlock) PROBE(__attribute__((amdgpu_waves_per_eu(ST
                 A.missed += nvalid - nmaybe;
                 pc_seen += nvalid;
                 pc_kept += nmaybe;
-                if (pc_on && pc_seen >= 256u && 5u * pc_kept > 3u * pc_seen) {
-                  pc_on = false;
-                  pc_off_now = true;
-                }
+                pc_on = pc_on && !yields_little();
                 PROBE(probe_add<kPrEstBatches>(pr, 1u); probe_add<kPrEstLanes>(pr, nvalid);
                       probe_add<kPrEstKept>(pr, nmaybe);)
                 __builtin_amdgcn_wave_barrier();
@@ -1076,7 +1154,7 @@ __global__ __launch_bounds__(kBlock) PROBE(__attribute__((amdgpu_waves_per_eu(ST
             __builtin_amdgcn_wave_barrier();
           }
         }
-        // nothing in flight and nothing left: the wave is done with the entry
+        // nothing in flight and nothing left: the wave is done with the part
         // (with no lane live but particles left, the next iteration claims more)
         if (ballot(L.live) == 0ull && exhausted && q_count == 0 && s_count == 0) break;
         make_ray(r, L.ox, L.oy, L.oz, L.wx, L.wy, L.wz);
@@ -1108,9 +1186,7 @@ __global__ __launch_bounds__(kBlock) PROBE(__attribute__((amdgpu_waves_per_eu(ST
       PROBE(probe_since<kPrTravCyc>(pr, kPrTp);)
     }
     PROBE(probe_set<kPrTc>(pr, probe_now());)
-    if (kPre && pc_off_now && lane == 0)  // published when the wave leaves the entry, outside the trace loop
-      __hip_atomic_store(a.scal_base + q.scalar_offset + kPrecullOff, 1ll, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (!kWave) __syncthreads();  // every wave is done with the entry; entry_sh / tile_sh may be reused
+    if (!kWave) __syncthreads();  // every wave is done with the part; part_sh / unit_sh may be reused
   }
   PROBE(probe_set<kPrWaves>(pr, 1u); probe_set<kPrCycles>(pr, probe_now() - probe_get(pr, kPrTs));
         if (lane < kProbeSlots) atomicAdd(&g_probe[lane], (unsigned long long)pr);)
@@ -1158,13 +1234,33 @@ __global__ __launch_bounds__(kBlock) void reduce_batch_kernel(const QueryDev* __
 
 // F/q = K sum(w - w'), K = 2 Gamma_hat / (N S^2) (eq. drag with the effective
 // mass of Sec. II.A); moment about x_ref from the moment about the CV centre.
-__global__ void finalize_kernel(const QueryDev* __restrict__ qs, const uint32_t* __restrict__ idx,
-                                const long long* __restrict__ scal_base, uint32_t nq, double xr, double yr, double zr,
-                                double A_ref, ResultDev* __restrict__ out) {
-  const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= nq) return;
-  const QueryDev& q = qs[idx ? idx[i] : i];
-  const long long* s = scal_base + q.scalar_offset;
+// One workgroup per query: thread (c, k) adds up slot k of copies c, c + 8, ...
+// (consecutive words, so a copy is one load of half a wave), thread 0 converts.
+__global__ __launch_bounds__(kBlock) void finalize_kernel(const QueryDev* __restrict__ qs,
+                                                          const uint32_t* __restrict__ idx,
+                                                          const long long* __restrict__ scal_base, ScalCopies copies,
+                                                          double xr, double yr, double zr, double A_ref,
+                                                          ResultDev* __restrict__ out) {
+  constexpr uint32_t kRows = kBlock / kScalStride;
+  __shared__ long long part[kRows][kScalStride], s[kScalStride];
+  const uint32_t i = blockIdx.x, j = idx ? idx[i] : i;
+  const QueryDev& q = qs[j];
+  const uint32_t k = threadIdx.x % kScalStride, row = threadIdx.x / kScalStride;
+  long long v = row == 0 && k < (uint32_t)kScalarSlots ? scal_base[q.scalar_offset + k] : 0;
+  if (copies.base) {
+    const long long* c = copies.base + ((uint64_t)j << copies.log2) * kScalStride + k;
+#pragma unroll 8
+    for (uint32_t r = row; r < (1u << copies.log2); r += kRows) v += c[(uint64_t)r * kScalStride];
+  }
+  part[row][k] = v;
+  __syncthreads();
+  if (threadIdx.x < (uint32_t)kScalStride) {
+    v = 0;
+    for (uint32_t r = 0; r < kRows; ++r) v += part[r][threadIdx.x];
+    s[threadIdx.x] = v;
+  }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
   const double N = (double)q.N;
   double F[3], Lc[3];
   for (int k = 0; k < 3; ++k) {
@@ -1258,13 +1354,17 @@ static_assert(sizeof(QueryDev) % 8 == 0 && kScalarSlots <= kBlock, "admission co
 // Serving admission, entry blockIdx.y: the slot's constants and cleared
 // scalar block (first workgroup), its per-triangle tally words (all).
 __global__ __launch_bounds__(kBlock) void admit_kernel(const AdmitRec* __restrict__ rec, QueryDev* __restrict__ qs,
-                                                       long long* __restrict__ scal, long long* __restrict__ tally) {
+                                                       long long* __restrict__ scal, ScalCopies copies,
+                                                       long long* __restrict__ tally) {
   const AdmitRec& r = rec[blockIdx.y];
   if (blockIdx.x == 0) {
     const uint64_t* src = reinterpret_cast<const uint64_t*>(&r.q);
     uint64_t* dst = reinterpret_cast<uint64_t*>(qs + r.slot);
     for (uint32_t w = threadIdx.x; w < sizeof(QueryDev) / 8; w += kBlock) dst[w] = src[w];
     if (threadIdx.x < (uint32_t)kScalarSlots) scal[(uint64_t)r.slot * kScalarSlots + threadIdx.x] = 0;
+    if (copies.base)
+      for (uint32_t w = threadIdx.x; w < (uint32_t)kScalStride << copies.log2; w += kBlock)
+        copies.base[(((uint64_t)r.slot << copies.log2) * kScalStride) + w] = 0;
   }
   for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < r.tally_words; i += (uint64_t)gridDim.x * kBlock)
     tally[r.tally_off + i] = 0;
@@ -1273,10 +1373,10 @@ __global__ __launch_bounds__(kBlock) void admit_kernel(const AdmitRec* __restric
 }  // namespace
 
 void launch_admit(const AdmitRec* rec, uint32_t n, uint64_t max_words, QueryDev* qs, long long* scal,
-                  long long* tally, hipStream_t st) {
+                  const ScalCopies& copies, long long* tally, hipStream_t st) {
   const uint64_t gx = (max_words + kBlock - 1) / kBlock;
   const dim3 g((uint32_t)(gx < 1 ? 1 : (gx > 1024 ? 1024 : gx)), n);
-  admit_kernel<<<g, kBlock, 0, st>>>(rec, qs, scal, tally);
+  admit_kernel<<<g, kBlock, 0, st>>>(rec, qs, scal, copies, tally);
 }
 
 // Check of the two-stage seeding's estimate: over particles [0, n) of one
@@ -1362,6 +1462,12 @@ void zero_i64(long long* p, uint64_t n, hipStream_t st) {
   if (n) zero_i64_kernel<<<grid_for(n, 4096), kBlock, 0, st>>>(p, n);
 }
 
+void clear_ranges(const ClearRanges& r, hipStream_t st) {
+  uint64_t n = 0;
+  for (int k = 0; k < kClearRanges; ++k) n = std::max(n, r.n[k]);
+  if (n) clear_kernel<<<grid_for(n, 4096), kBlock, 0, st>>>(r);
+}
+
 void zero_u32(uint32_t* p, uint64_t n, hipStream_t st) {
   if (n) zero_u32_kernel<<<grid_for(n, 4096), kBlock, 0, st>>>(p, n);
 }
@@ -1389,13 +1495,35 @@ void launch_trace(const TraceArgs& a, int stack_slots, TallyMode mode, int grid,
   }
 }
 
-void launch_batch(const BatchArgs& a, int stack_slots, TallyMode mode, int grid, hipStream_t st) {
+void launch_batch(BatchArgs a, int stack_slots, TallyMode mode, uint64_t total_particles, bool uniform,
+                  uint64_t counters, int n_cu, int groups_per_cu, hipStream_t st) {
+  // workgroups resident per CU: at most four (four waves per SIMD at <= 128
+  // VGPRs; the mixed variant's 129-133 leave three), and what 160 KB of LDS holds
+  const size_t lds = tally_lds_bytes(mode, a.lds_tris, true, a.wave_totals != 0u) + (size_t)stack_slots * kBlock * 4 +
+                     (stack_slots <= 32 ? 7808u : 6784u);  // stack; queue, rings and claims of batch_kernel
+  int resident = (int)((160u << 10) / lds);
+  resident = std::max(1, std::min(resident, mode == kTallyAuto ? 3 : 4));
+  const uint64_t batches = (total_particles + 63) / 64;
+  uint64_t grid = (uint64_t)n_cu * (uint64_t)std::min(groups_per_cu, resident);
+  grid = std::max<uint64_t>(1, std::min<uint64_t>(grid, (batches + kWaves - 1) / kWaves));
+  const uint64_t waves = grid * kWaves;
+  a.sub_log2 = 0;
+  if (!uniform || batches > waves)  // more than one batch per wave: units are claimed, from up to 16 counters
+    while (((uint64_t)a.n_entries << (a.sub_log2 + 1)) <= std::min<uint64_t>(counters, 16)) ++a.sub_log2;
+  const uint64_t parts = (uint64_t)a.n_entries << a.sub_log2;
+  a.start_div = uniform ? (uint32_t)(grid / parts) : 0u;
+  a.start_rem = uniform ? (uint32_t)(grid % parts) : 0u;
+  a.xcd_cus = (uint32_t)std::max(1, n_cu / 8);
+  a.share_log2 = 6;
+  while ((waves << (a.share_log2 + 1)) <= total_particles) ++a.share_log2;
+  a.unit_cap_log2 = 0;
+  while ((128u << a.unit_cap_log2) <= a.tile / 4 && a.unit_cap_log2 < 8) ++a.unit_cap_log2;
   switch (stack_slots) {
-    case 4: launch_batch_mode<4>(a, mode, grid, st); break;
-    case 8: launch_batch_mode<8>(a, mode, grid, st); break;
-    case 16: launch_batch_mode<16>(a, mode, grid, st); break;
-    case 32: launch_batch_mode<32>(a, mode, grid, st); break;
-    default: launch_batch_mode<64>(a, mode, grid, st); break;
+    case 4: launch_batch_mode<4>(a, mode, (int)grid, st); break;
+    case 8: launch_batch_mode<8>(a, mode, (int)grid, st); break;
+    case 16: launch_batch_mode<16>(a, mode, (int)grid, st); break;
+    case 32: launch_batch_mode<32>(a, mode, (int)grid, st); break;
+    default: launch_batch_mode<64>(a, mode, (int)grid, st); break;
   }
 }
 
@@ -1410,9 +1538,9 @@ void launch_reduce_batch(const QueryDev* d_qs, uint32_t nq, long long* tally_bas
   reduce_batch_kernel<<<g, kBlock, 0, st>>>(d_qs, tally_base, scal_base);
 }
 
-void launch_finalize(const QueryDev* d_qs, const uint32_t* d_idx, const long long* scal_base, uint32_t nq, double xr,
-                     double yr, double zr, double A_ref, ResultDev* out, hipStream_t st) {
-  finalize_kernel<<<(nq + 63) / 64, 64, 0, st>>>(d_qs, d_idx, scal_base, nq, xr, yr, zr, A_ref, out);
+void launch_finalize(const QueryDev* d_qs, const uint32_t* d_idx, const long long* scal_base, const ScalCopies& copies,
+                     uint32_t nq, double xr, double yr, double zr, double A_ref, ResultDev* out, hipStream_t st) {
+  finalize_kernel<<<nq, kBlock, 0, st>>>(d_qs, d_idx, scal_base, copies, xr, yr, zr, A_ref, out);
 }
 
 // Per-triangle reduction of a list of slots (serving): entry y reduces slot idx[y].

@@ -14,6 +14,17 @@ namespace tpmc {
 // that mix both kinds of request).
 enum TallyMode { kTallyGlobal = 0, kTallyLds = 1, kTallyLane = 2, kTallyTotals = 3, kTallyAuto = 4 };
 
+// Copies of the queries' scalar blocks: copy c of query i at
+// base + ((i << log2) + c) * kScalStride (base null: none, the block itself is
+// added into).  Workgroup b adds into copy b % 2^log2, finalize_kernel sums
+// them.  One address takes an atomic every 12 ns, so the 12 sums of each of
+// 4096 waves on one block took 355 us; workgroups b, b + 8, ... run on one XCD,
+// so a copy's cache line also stays in that XCD's L2 (eight copies: 49 us).
+struct ScalCopies {
+  long long* base;
+  uint32_t log2;
+};
+
 struct TraceArgs {
   const Node* nodes;
   const TriRec* tris;
@@ -24,6 +35,8 @@ struct TraceArgs {
   uint64_t n;
   long long* tally;           // [nt][7] or null (totals mode)
   long long* scal;            // [kScalarSlots]
+  long long* copies;          // the query's ScalCopies (null: none), 1 + copy_mask of them
+  uint32_t copy_mask;
   int32_t* first_tri;         // optional, already offset to the query
   unsigned long long* counters;  // optional [2]: BVH nodes visited, triangle tests
   uint32_t nt;
@@ -31,34 +44,53 @@ struct TraceArgs {
 };
 
 // One persistent launch covers n_entries entries; entry j is entry_tiles[j]
-// tiles of query entry_query[j] starting at tile entry_tile0[j] (a whole batch:
-// entry j = query j from tile 0; a serving step: any slots, any ranges).
-// Waves claim work entry by entry in units of a quarter tile (a whole tile
-// when the tile is not a multiple of 256 particles; entry_next[j] counts the
-// claimed units), so a wave stays on one query and flushes its partial sums
-// only when it moves to another.  With workgroup LDS tallies the workgroup's
-// waves move to another entry together.
+// tiles of query entry_query[j] starting at tile entry_tile0[j] (a serving
+// step: any slots, any ranges), or, with null lists, all particles of query j
+// (a whole batch).  Each entry is cut into 2^sub_log2 parts with a claim
+// counter each (entry_next[j << sub_log2 | part]), so that the waves of a
+// launch with few queries do not all claim from one address (12 ns per atomic
+// on one address, measured).  A part is handed out in units of whole
+// 64-particle batches (UnitPlan in tpmc_kernels.hip): one unit per wave that
+// starts on it, taken without an atomic, then units by the counter that halve
+// in size towards the part's end.  A wave stays on one query and flushes its
+// partial sums only when it moves to another.  With workgroup LDS tallies the
+// workgroup's waves move to another part together.
 struct BatchArgs {
   const QueryDev* qs;              // query / slot table (meshes referenced per query)
   const uint32_t* entry_query;     // [n_entries] or null (entry j is query j)
   const uint64_t* entry_tile0;     // [n_entries] or null (start at tile 0)
-  const uint64_t* entry_tiles;     // [n_entries] tiles to trace per entry
-  unsigned long long* entry_next;  // [n_entries] claim counters, zeroed before the launch
+  const uint64_t* entry_tiles;     // [n_entries] or null (every tile of the query)
+  unsigned long long* entry_next;  // [n_entries << sub_log2] claim counters, zeroed before the launch
   long long* tally_base;           // per-triangle tallies, indexed by QueryDev::tally_offset
   long long* scal_base;            // scalar blocks, indexed by QueryDev::scalar_offset
+  ScalCopies copies;               // of the blocks of qs
   uint32_t n_entries;
+  uint32_t sub_log2;               // parts per entry (log2)
   uint32_t refill;                 // as TraceArgs::refill
-  uint64_t tile;                   // particles per tile (multiple of 64)
+  uint32_t tile;                   // particles per tile (multiple of 64)
+  uint32_t unit_cap_log2;          // no unit exceeds 64 << unit_cap_log2 particles (<= 8: 16-bit offsets in a unit)
+  uint32_t share_log2;             // particles per wave of the whole launch (log2, rounded down)
+  // Starting parts taken without an atomic (0, 0: none): start_div workgroups
+  // start on each part, one more on each of the first start_rem.
+  uint32_t start_div, start_rem;
+  uint32_t xcd_cus;                // compute units per XCD
   uint32_t lds_tris;               // largest nt of an entry with an LDS tally (kTallyLds / kTallyAuto)
   uint32_t wave_totals;            // kTallyAuto: some entry keeps totals only (per-wave LDS totals allocated)
-  // Where each XCD's workgroups start claiming: XCD x (workgroups x, x + 8, ...; the
-  // hardware deals workgroups to the eight XCDs in turn) starts in entries
-  // [xcd_start[x], xcd_start[x + 1]) (entries grouped by mesh, ranges by tile share),
-  // so that each XCD's L2 holds the hierarchies of few meshes; all 0: entry
-  // blockIdx % n_entries.
+  // Where each XCD's workgroups start claiming without a starting part: XCD x
+  // (workgroups x, x + 8, ...; the hardware deals workgroups to the eight XCDs
+  // in turn) starts in entries [xcd_start[x], xcd_start[x + 1]) (entries
+  // grouped by mesh, ranges by tile share), so that each XCD's L2 holds the
+  // hierarchies of few meshes.
   uint32_t xcd_start[9];
 };
 
+// Word ranges cleared by one launch (n 0: none).
+constexpr int kClearRanges = 4;
+struct ClearRanges {
+  long long* p[kClearRanges];
+  uint64_t n[kClearRanges];
+};
+void clear_ranges(const ClearRanges& r, hipStream_t st);
 void zero_i64(long long* p, uint64_t n, hipStream_t st);
 // Fills the seeding start table of the current device (once per device).
 hipError_t init_seed_tables(hipStream_t st);
@@ -82,11 +114,16 @@ int stack_slots_for_depth(uint32_t depth);  // 0 when too deep
 void launch_seed(const QueryDev* d_q, uint64_t n, float* const x[3], float* const w[3], int grid, hipStream_t st);
 void launch_trace(const TraceArgs& a, int stack_slots, TallyMode mode, int grid, hipStream_t st);
 void launch_reduce(const long long* tally, uint32_t nt, long long* scal, hipStream_t st);
-void launch_finalize(const QueryDev* d_qs, const uint32_t* d_idx, const long long* scal_base, uint32_t nq, double xr,
-                     double yr, double zr, double A_ref, ResultDev* out, hipStream_t st);
+void launch_finalize(const QueryDev* d_qs, const uint32_t* d_idx, const long long* scal_base, const ScalCopies& copies,
+                     uint32_t nq, double xr, double yr, double zr, double A_ref, ResultDev* out, hipStream_t st);
 void launch_reduce_slots(const QueryDev* d_qs, const uint32_t* d_idx, uint32_t n, long long* tally_base,
                          long long* scal_base, uint32_t max_nt, hipStream_t st);
-void launch_batch(const BatchArgs& a, int stack_slots, TallyMode mode, int grid, hipStream_t st);
+// Launches at most max_grid workgroups over total_particles: no more than are
+// resident at once and no more than there are batches for.  uniform: every
+// entry may be started on without an atomic (a batch); sub_log2, the shares and
+// the starting parts of a are set here; counters: words at a.entry_next.
+void launch_batch(BatchArgs a, int stack_slots, TallyMode mode, uint64_t total_particles, bool uniform,
+                  uint64_t counters, int n_cu, int groups_per_cu, hipStream_t st);
 // Check of the two-stage seeding's estimate (precull_check_kernel): out[0] the
 // bits of the largest error / margin, out[1] the particles estimated.
 void launch_precull_check(const QueryDev* d_q, uint64_t n, unsigned long long* out, int grid, hipStream_t st);
@@ -96,9 +133,9 @@ void launch_precull_check(const QueryDev* d_q, uint64_t n, unsigned long long* o
 bool probe_built();
 hipError_t probe_read(unsigned long long* out, bool reset, hipStream_t st);
 // Serving admission: n records (device) -> constants into qs[slot], cleared
-// scalar block and per-triangle tally words; max_words is the largest tally.
+// scalar block (and copies) and per-triangle tally words; max_words is the largest tally.
 void launch_admit(const AdmitRec* rec, uint32_t n, uint64_t max_words, QueryDev* qs, long long* scal,
-                  long long* tally, hipStream_t st);
+                  const ScalCopies& copies, long long* tally, hipStream_t st);
 
 // Ceiling microkernels (tpmc_ceilings.hip).  kind 0: FP32 FMA, 1: FP64 FMA,
 // 2: int32 multiply and add; each lane performs ceiling_valu_ops_per_lane(iters)
