@@ -1154,9 +1154,11 @@ __global__ __launch_bounds__(kBlock) PROBE(__attribute__((amdgpu_waves_per_eu(ST
             __builtin_amdgcn_wave_barrier();
           }
         }
-        // nothing in flight and nothing left: the wave is done with the part
-        // (with no lane live but particles left, the next iteration claims more)
-        if (ballot(L.live) == 0ull && exhausted && q_count == 0 && s_count == 0) break;
+        // nothing in flight and nothing left: the wave is done with the part.  It
+        // stays until the part is dry (with no lane live but particles or units
+        // left, the next iteration claims more): others may leave the part's
+        // last units to it (claim_any).
+        if (ballot(L.live) == 0ull && dry && exhausted && q_count == 0 && s_count == 0) break;
         make_ray(r, L.ox, L.oy, L.oz, L.wx, L.wy, L.wz);
         guard = 0;
       }

@@ -1,6 +1,7 @@
 """Batched launches at the sizes where the cut into units changes: fewer
 particles than a batch, than one batch per wave, just above, uneven queries in
-one launch, and a workspace without room for the copies of the scalar sums.
+one launch, many small queries (whose last units only the waves that started
+on them take), and a workspace without room for the copies of the scalar sums.
 Every result equals the plain path's bit for bit."""
 import ctypes
 
@@ -34,10 +35,11 @@ def _same(T, plain, got, what):
 
 @pytest.mark.parametrize("kind", sorted(MESHES))
 @pytest.mark.parametrize("totals", [False, True])
-@pytest.mark.parametrize("sizes", [(1,), (63, 64, 65), (1000, 1, 130_000), (262_143,), (262_209, 5), (700_001,)])
+@pytest.mark.parametrize("sizes", [(1,), (63, 64, 65), (1000, 1, 130_000), (262_143,), (262_209, 5), (700_001,),
+                                   tuple(16_200 + i for i in range(150))], ids=lambda s: "x".join(map(str, s[:4])))
 def test_batch_equals_plain_at_unit_edges(ctx, T, kind, totals, sizes):
     mesh = ctx.build_mesh(*MESHES[kind]())
-    qs = [I.query(q=tuple(qq), S=3.0 + i, alpha=0.9, n=n, seed=40 + i, flags=1 if totals else 0)
+    qs = [I.query(q=tuple(qq), S=3.0 + i % 7, alpha=0.9, n=n, seed=40 + i, flags=1 if totals else 0)
           for i, (n, qq) in enumerate(zip(sizes, I.random_quats(len(sizes), 3)))]
     plain, pr = T.run(mesh, qs, A_ref=1.0)
     pr.close()
