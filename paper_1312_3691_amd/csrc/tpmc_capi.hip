@@ -586,7 +586,7 @@ extern "C" tpmc_status tpmc_build_mesh_ex(tpmc_ctx ctx, const float* xyz, uint64
             : build_bvh(d_xyz, d_tri, nt, lo, hi, scratch, m->nodes, m->tris, m->orig, &depth, ctx->stream);
   }
   if (e == hipSuccess) {
-    mark_support(d_xyz, nv, m->tris, nt, m->orig, ctx->stream);
+    mark_support(d_xyz, nv, m->tris, nt, m->orig, scratch, ctx->stream);
     e = hipStreamSynchronize(ctx->stream);
     if (e == hipSuccess) e = hipGetLastError();
   }
