@@ -94,6 +94,8 @@ struct Layout {
   float* planes[6];
   ScalCopies copies;         // of the scalar blocks; none where the workspace has no room for them
   uint64_t copy_words;
+  TallyCopies tally_copies;  // of the per-triangle tallies; none where not worth it or without room
+  uint64_t tally_words;
   uint64_t need;             // bytes without the copies
   uint64_t bytes;            // bytes with them
 };
@@ -118,7 +120,6 @@ struct tpmc_batch_s {
   uint32_t nq;
   std::vector<QueryDev> hq;
   Layout lay;
-  uint64_t tally_words;
   TallyMode mode;
   int n_cu, groups_per_cu;
   uint64_t total_particles;
@@ -404,6 +405,14 @@ static uint32_t copies_log2(uint64_t nq, uint64_t waves) {
 }
 constexpr uint64_t kMostWaves = 4096;  // resident waves of a launch on 256 compute units
 
+// Copies (log2) of the per-triangle tallies: meshes of one or two triangles are
+// flushed by every wave (14 sums), as the scalar blocks are (2e5 particles on
+// the plate: 205 us with one copy, 42 with 32).  Larger meshes' hits and
+// flushes are spread over more cache lines.
+static uint32_t tally_copies_log2(uint64_t nq, uint64_t nt, uint64_t waves) {
+  return nt <= (uint64_t)kLaneTallyMaxTris ? copies_log2(nq, waves) : 0u;
+}
+
 // Lays out [queries | results | scalar blocks | tallies | claim counters | 6 planes | copies of the scalar blocks]
 // in ws_bytes at base.
 static void layout(std::vector<QueryDev>& hq, uint64_t nt, uint64_t n_planes, bool batch, uint8_t* base,
@@ -429,12 +438,19 @@ static void layout(std::vector<QueryDev>& hq, uint64_t nt, uint64_t n_planes, bo
   uint64_t o_p[6];
   for (int k = 0; k < 6; ++k) o_p[k] = take(n_planes * sizeof(float));
   L.need = off;
-  const uint32_t cl = copies_log2(nq, std::min<uint64_t>(kMostWaves, total_particles(hq) / 64));
+  const uint64_t waves = std::min<uint64_t>(kMostWaves, total_particles(hq) / 64);
+  const uint32_t cl = copies_log2(nq, waves), tl = words ? tally_copies_log2(nq, nt, waves) : 0;
   L.copy_words = cl ? (nq << cl) * kScalStride : 0;
   const uint64_t o_sc = take(L.copy_words * sizeof(long long));
+  const uint64_t with_scal = off;
+  L.tally_words = words;
+  const uint64_t stride = (words + 31) & ~31ull;  // whole cache lines
+  const uint64_t o_tc = take(tl ? (stride << tl) * sizeof(long long) : 0);
   L.bytes = off;
+  L.tally_copies = TallyCopies{reinterpret_cast<long long*>(base + o_tc), tl, stride};
+  if (tl == 0 || ws_bytes < L.bytes) L.tally_copies = TallyCopies{nullptr, 0, 0};
   L.copies = ScalCopies{reinterpret_cast<long long*>(base + o_sc), cl};
-  if (cl == 0 || ws_bytes < L.bytes) {
+  if (cl == 0 || ws_bytes < with_scal) {
     L.copies = ScalCopies{nullptr, 0};
     L.copy_words = 0;
   }
@@ -704,10 +720,10 @@ extern "C" tpmc_status tpmc_seed(tpmc_ctx ctx, tpmc_mesh m, const tpmc_query* q,
     delete p;
     return fail(TPMC_E_DEVICE, "query upload: %s", hipGetErrorString(e));
   }
-  uint64_t words = 0;
-  for (const auto& hq : p->hq) words += hq.per_tri ? m->nt * 7 : 0;
-  clear_ranges({{p->lay.scal, p->lay.tally, p->lay.copies.base, nullptr},
-                {(uint64_t)nq * kScalarSlots, words, p->lay.copy_words, 0}}, ctx->stream);
+  const TallyCopies& tc = p->lay.tally_copies;
+  clear_ranges({{p->lay.scal, p->lay.tally, p->lay.copies.base, tc.base, nullptr},
+                {(uint64_t)nq * kScalarSlots, p->lay.tally_words, p->lay.copy_words, tc.stride << tc.log2, 0}},
+               ctx->stream);
   for (uint32_t i = 0; i < nq; ++i) {
     const QueryDev& hq = p->hq[i];
     float* const x[3] = {p->lay.planes[0] + hq.p_offset, p->lay.planes[1] + hq.p_offset,
@@ -767,6 +783,9 @@ extern "C" tpmc_status tpmc_trace_ex(tpmc_ctx ctx, tpmc_mesh m, tpmc_particles p
     const ScalCopies& sc = p->lay.copies;
     a.copies = sc.base ? sc.base + ((uint64_t)i << sc.log2) * kScalStride : nullptr;
     a.copy_mask = (1u << sc.log2) - 1u;
+    a.tally_copies = p->lay.tally_copies;
+    if (!hq.per_tri) a.tally_copies.base = nullptr;
+    if (a.tally_copies.base) a.tally_copies.base += hq.tally_offset;
     a.first_tri = dev_first_tri ? dev_first_tri + hq.p_offset : nullptr;
     a.counters = reinterpret_cast<unsigned long long*>(dev_counters);
     a.nt = (uint32_t)m->nt;
@@ -774,6 +793,8 @@ extern "C" tpmc_status tpmc_trace_ex(tpmc_ctx ctx, tpmc_mesh m, tpmc_particles p
     launch_trace(a, m->stack_slots, plain_mode(hq, m->nt), trace_grid(ctx, hq.N), ctx->stream);
     HIP_CHECK_LAUNCH("trace");
   }
+  if (p->lay.tally_copies.base) launch_fold_tally(p->lay.tally, p->lay.tally_copies, ctx->stream);
+  HIP_CHECK_LAUNCH("tally fold");
   tpmc_tally t = new (std::nothrow) tpmc_tally_s;
   if (!t) return fail(TPMC_E_INVALID, "out of host memory");
   t->p = p;
@@ -913,10 +934,8 @@ static tpmc_status batch_init(tpmc_ctx ctx, tpmc_mesh m, const tpmc_query* q, ui
   b->device = ctx->device;
   b->mesh = m;
   b->nq = nq;
-  b->tally_words = 0;
   bool any_tri = false, all_tri = true;
   for (const auto& hq : b->hq) {
-    b->tally_words += hq.per_tri ? m->nt * 7 : 0;
     any_tri = any_tri || hq.per_tri;
     all_tri = all_tri && hq.per_tri;
   }
@@ -958,8 +977,10 @@ extern "C" tpmc_status tpmc_batch_create(tpmc_ctx ctx, tpmc_mesh m, const tpmc_q
 
 static void batch_enqueue(tpmc_batch b, hipStream_t st) {
   tpmc_mesh m = b->mesh;
-  clear_ranges({{reinterpret_cast<long long*>(b->lay.next), b->lay.scal, b->lay.tally, b->lay.copies.base},
-                {b->lay.counters, (uint64_t)b->nq * kScalarSlots, b->tally_words, b->lay.copy_words}}, st);
+  const TallyCopies& tc = b->lay.tally_copies;
+  clear_ranges({{reinterpret_cast<long long*>(b->lay.next), b->lay.scal, b->lay.tally, b->lay.copies.base, tc.base},
+                {b->lay.counters, (uint64_t)b->nq * kScalarSlots, tc.base ? 0 : b->lay.tally_words,
+                 b->lay.copy_words, tc.stride << tc.log2}}, st);
   BatchArgs a{};
   a.qs = b->lay.qs;
   a.entry_query = nullptr;
@@ -969,13 +990,14 @@ static void batch_enqueue(tpmc_batch b, hipStream_t st) {
   a.tally_base = b->lay.tally;
   a.scal_base = b->lay.scal;
   a.copies = b->lay.copies;
+  a.tally_copies = tc;
   a.n_entries = b->nq;
   a.refill = b->refill;
   a.tile = b->tile;
   a.lds_tris = b->mode == kTallyLds ? (uint32_t)m->nt : 0u;
   a.wave_totals = b->mode == kTallyTotals ? 1u : 0u;
   launch_batch(a, m->stack_slots, b->mode, b->total_particles, true, b->lay.counters, b->n_cu, b->groups_per_cu, st);
-  if (b->mode != kTallyTotals) launch_reduce_batch(b->lay.qs, b->nq, b->lay.tally, b->lay.scal, (uint32_t)m->nt, st);
+  if (b->mode != kTallyTotals) launch_reduce_batch(b->lay.qs, b->nq, b->lay.tally, tc, b->lay.scal, (uint32_t)m->nt, st);
 }
 
 extern "C" tpmc_status tpmc_batch_launch(tpmc_ctx ctx, tpmc_batch b, int use_graph) {

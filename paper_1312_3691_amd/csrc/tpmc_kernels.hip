@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <utility>
 
 #include "tpmc_device.hpp"
 #include "tpmc_launch.h"
@@ -379,6 +380,14 @@ __device__ __forceinline__ void acc_zero(Acc& A) {
 
 __device__ __forceinline__ uint64_t lanes(bool p) { return (uint64_t)__popcll(__builtin_amdgcn_ballot_w64(p)); }
 
+// The lane number as a value of its own: comparisons with it are not moved out of
+// the loops around (a mask of two scalar registers each, held throughout).
+__device__ __forceinline__ uint32_t local_lane() {
+  uint32_t l = threadIdx.x & 63u;
+  __asm__ volatile("" : "+v"(l));
+  return l;
+}
+
 // Set bits of a wave mask below the calling lane (v_mbcnt; no per-lane mask kept live).
 __device__ __forceinline__ uint32_t below(uint64_t m) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
@@ -491,13 +500,53 @@ __device__ __forceinline__ void retire(const QueryDev& q, const Lane& L, Acc& A)
   A.sE2 += fx(L.E * L.E, q.scaleE2);
 }
 
+// Per-triangle sums of a pass's hits, added in device memory with eight lanes to
+// a hit: seven consecutive words per triangle go out in one instruction, and
+// the L2 takes them as one or two cache-line requests.  With a lane to a hit
+// and an instruction to a word every lane is a request of its own: 23e9 atomics/s
+// for the chip against 92e9 this way (any number of triangles from 1280 to
+// 50000, measured).  4e6 particles on a 1280-triangle sphere: 3.78 ms before,
+// 1.10 now, 0.67 with totals alone.  A lane with a hit has no segment in flight, so its column of the
+// traversal stack is free: the hit's values are handed over there.  Called by
+// every lane of the wave (convergent).
+template <int STACK>
+__device__ __forceinline__ void tally_rows(const QueryDev& q, const Hit& h, long long* __restrict__ g,
+                                           int (*stk)[kBlock]) {
+  const uint64_t m = ballot(h.valid);
+  if (m == 0ull) return;
+  const uint32_t lane = local_lane(), first = threadIdx.x & ~63u;
+  if (h.valid) {
+    stk[0][threadIdx.x] = (int)rintf(h.dx * q.scaleF);
+    stk[1][threadIdx.x] = (int)rintf(h.dy * q.scaleF);
+    stk[2][threadIdx.x] = (int)rintf(h.dz * q.scaleF);
+    stk[3][threadIdx.x] = (int)rintf(h.lx * q.scaleL);
+    stk[4][threadIdx.x] = (int)rintf(h.ly * q.scaleL);
+    stk[5][threadIdx.x] = (int)rintf(h.lz * q.scaleL);
+    stk[6][threadIdx.x] = 1;
+    stk[7][threadIdx.x] = (int)h.id;
+  }
+  const uint32_t n = (uint32_t)__popcll(m);
+  // lane o < n learns the lane of the o-th hit
+  const int from = __builtin_amdgcn_ds_permute((int)((h.valid ? below(m) : n + below(~m)) * 4u), (int)lane);
+  __builtin_amdgcn_wave_barrier();
+  for (uint32_t o = lane >> 3; o - (lane >> 3) < n; o += 8u) {
+    const uint32_t col = first + (uint32_t)__builtin_amdgcn_ds_bpermute((int)((o & 63u) * 4u), from), c = lane & 7u;
+    if (o < n && c < 7u) atomic_add_i64(g + 7ull * (uint32_t)stk[7][col] + c, (long long)stk[c][col]);
+  }
+  __builtin_amdgcn_wave_barrier();
+}
+
 // Tally of one hit per lane.  Called by every lane of the wave (convergent).
 // Totals-only sums go to the wave's LDS slots lds[c][wave] (LDS atomics; the
 // few lanes of a pass with a hit share them) when TOT_LDS (the persistent
 // kernel, short of registers), else to the lane's registers.
-template <int MODE, bool TOT_LDS = true>
+template <int MODE, int STACK, bool TOT_LDS = true>
 __device__ __forceinline__ void tally(const QueryDev& q, const Hit& h, long long* __restrict__ g,
-                                      unsigned long long* lds, uint32_t nt, Acc& A) {
+                                      unsigned long long* lds, int (*stk)[kBlock], Acc& A) {
+  if (STACK >= 8 && (MODE == kTallyGlobal || (MODE == kTallyAuto && q.per_tri))) {
+    tally_rows<STACK>(q, h, g, stk);
+    return;
+  }
   long long v[7];
   // one hit's values are below 2^30 in magnitude after scaling (scale choice)
   v[0] = fx32(h.dx, q.scaleF); v[1] = fx32(h.dy, q.scaleF); v[2] = fx32(h.dz, q.scaleF);
@@ -531,15 +580,37 @@ __device__ __forceinline__ void tally(const QueryDev& q, const Hit& h, long long
   }
 }
 
-// Flush (and clear) the calling lane's per-lane tallies of a <= 2-triangle
-// mesh: one wave sum per slot, one atomic per wave (convergent).
-__device__ __forceinline__ void flush_lane_tally(unsigned long long* lds, long long* __restrict__ g, uint32_t nt) {
-#pragma unroll
-  for (int c = 0; c < 2 * 7; ++c) {
-    const long long s = wave_sum((long long)lds[c * kBlock + threadIdx.x]);
-    lds[c * kBlock + threadIdx.x] = 0ull;
-    if ((threadIdx.x & 63) == 0 && s != 0 && c < (int)nt * 7) atomic_add_i64(g + c, s);
+// Wave-uniform 64-bit values, one per lane: lane k holds the k-th (0 if none).
+// Written with v_writelane straight from scalar registers: a select per lane
+// would have the compiler hold the values in vector registers throughout.
+struct LaneSums {
+  int lo = 0, hi = 0;
+  template <int K>
+  __device__ __forceinline__ void put(long long v) {
+    // the wait states keep a scalar written, or the VGPR read, by a vector
+    // instruction next to it exact
+    asm("s_nop 1\n\tv_writelane_b32 %0, %1, %2\n\ts_nop 1" : "+v"(lo) : "s"((uint32_t)v), "i"(K));
+    asm("s_nop 1\n\tv_writelane_b32 %0, %1, %2\n\ts_nop 1" : "+v"(hi) : "s"((uint32_t)((unsigned long long)v >> 32)), "i"(K));
   }
+  __device__ __forceinline__ long long get() const {
+    return (long long)(((unsigned long long)(uint32_t)hi << 32) | (uint32_t)lo);
+  }
+};
+
+template <int... C>
+__device__ __forceinline__ void lane_tally_sums(LaneSums& sums, unsigned long long* lds, std::integer_sequence<int, C...>) {
+  ((sums.put<C>(wave_sum_uniform((long long)lds[C * kBlock + threadIdx.x])), lds[C * kBlock + threadIdx.x] = 0ull), ...);
+}
+
+// Flush (and clear) the calling lane's per-lane tallies of a <= 2-triangle
+// mesh: one wave sum per slot, lane k then adds slot k: one atomic instruction
+// per wave (convergent).
+__device__ __forceinline__ void flush_lane_tally(unsigned long long* lds, long long* __restrict__ g, uint32_t nt) {
+  const uint32_t lane = local_lane();
+  LaneSums sums;
+  lane_tally_sums(sums, lds, std::make_integer_sequence<int, 2 * 7>{});
+  const long long mine = sums.get();
+  if (lane < 7u * nt && lane < 14u && mine != 0) atomic_add_i64(g + lane, mine);
 }
 
 // Wave-reduce the per-lane accumulators into a query's scalar block.  With
@@ -597,6 +668,9 @@ __global__ __launch_bounds__(kBlock) void trace_kernel(TraceArgs a) {
   __shared__ int stk[STACK][kBlock];
   extern __shared__ unsigned long long lt[];  // tallies in LDS, sized at launch (tally_lds_bytes)
   const QueryDev& q = *a.q;
+  long long* const g_tally = a.tally_copies.base
+                                 ? a.tally_copies.base + (blockIdx.x & ((1u << a.tally_copies.log2) - 1u)) * a.tally_copies.stride
+                                 : a.tally;
   if (MODE == kTallyLds) {
     for (uint32_t i = threadIdx.x; i < a.nt * 7u; i += kBlock) lt[i] = 0ull;
     __syncthreads();
@@ -644,7 +718,7 @@ __global__ __launch_bounds__(kBlock) void trace_kernel(TraceArgs a) {
         bool limited = false;
         if (fin) out = finish_segment(a.tris, a.orig, q, L, s, h, fid, limited);
         count_pass(A, fin, out, h.valid, limited);
-        tally<MODE, false>(q, h, a.tally, lt, a.nt, A);
+        tally<MODE, STACK, false>(q, h, g_tally, lt, stk, A);
         if (fin) {
           if (a.first_tri && fid != -2) a.first_tri[L.pid] = fid;
           if (out != kOutGoOn) {
@@ -670,7 +744,7 @@ __global__ __launch_bounds__(kBlock) void trace_kernel(TraceArgs a) {
       trav_step<STACK, COUNT>(a.nodes, a.tris, a.orig, r, L.prev, s, stk, A.nodes, A.tests);
   }
   flush_acc(A, a.copies ? a.copies + (uint64_t)(blockIdx.x & a.copy_mask) * kScalStride : a.scal, MODE == kTallyTotals);
-  if (MODE == kTallyLane) flush_lane_tally(lt, a.tally, a.nt);
+  if (MODE == kTallyLane) flush_lane_tally(lt, g_tally, a.nt);
   if (COUNT) {
     const long long nn = wave_sum((long long)A.nodes), nt2 = wave_sum((long long)A.tests);
     if ((threadIdx.x & 63) == 0) {
@@ -681,7 +755,7 @@ __global__ __launch_bounds__(kBlock) void trace_kernel(TraceArgs a) {
   if (MODE == kTallyLds) {
     __syncthreads();
     for (uint32_t i = threadIdx.x; i < a.nt * 7u; i += kBlock)
-      if (lt[i]) atomic_add_i64(a.tally + i, (long long)lt[i]);
+      if (lt[i]) atomic_add_i64(g_tally + i, (long long)lt[i]);
   }
 }
 
@@ -751,9 +825,11 @@ __device__ __forceinline__ bool claim_counted(const BatchArgs& a, uint32_t part,
 // parts are looked at per step, one per lane (called by a whole wave; uniform
 // result, kNoEntry when there is none).  A failed claim on a part means that
 // it was used up meanwhile.  Where every part has waves that started on it
-// (they stay until it is used up), its last small units are left to them:
-// taking up another query, draining and flushing cost more than such a unit.
-constexpr uint64_t kJoinMin = 256;
+// (they stay until it is used up), its last units, below kJoinMin particles, are
+// left to them: taking up another query, draining and flushing cost more than
+// such a unit (kJoinMin 64 / 256 / 512 / 1024: plate sweep 2.17 / 2.10 / 2.06 /
+// 2.00 ms, cylinder sweep 6.91 / 6.84 / 6.72 / 6.73).
+constexpr uint64_t kJoinMin = 1024;
 __device__ __forceinline__ uint32_t claim_any(const BatchArgs& a, uint32_t scan, uint64_t& b, uint64_t& e) {
   const uint32_t parts = a.n_entries << a.sub_log2, lane = threadIdx.x & 63u;
   for (uint32_t k = 0; k < parts; k += 64u) {
@@ -804,6 +880,15 @@ __device__ __forceinline__ void start_part(const BatchArgs& a, uint32_t& part, u
 __device__ __forceinline__ long long* scal_block(const BatchArgs& a, uint32_t query, const QueryDev& q) {
   if (a.copies.base == nullptr) return a.scal_base + q.scalar_offset;
   return a.copies.base + (((uint64_t)query << a.copies.log2) + (blockIdx.x & ((1u << a.copies.log2) - 1u))) * kScalStride;
+}
+
+// Where the workgroup's waves add a query's per-triangle sums.
+__device__ __forceinline__ long long* tally_block(const BatchArgs& a, const QueryDev& q) {
+  if (!q.per_tri) return nullptr;
+  long long* const base = a.tally_copies.base
+                              ? a.tally_copies.base + (blockIdx.x & ((1u << a.tally_copies.log2) - 1u)) * a.tally_copies.stride
+                              : a.tally_base;
+  return base + q.tally_offset;
 }
 
 __device__ __forceinline__ uint64_t uniform_u64(uint64_t v) {
@@ -914,7 +999,7 @@ __global__ __launch_bounds__(kBlock) PROBE(__attribute__((amdgpu_waves_per_eu(ST
       const uint32_t hq = a.entry_query ? a.entry_query[held] : held;
       const QueryDev& qh = a.qs[hq];
       long long* const hscal = scal_block(a, hq, qh);
-      long long* htally = qh.per_tri ? a.tally_base + qh.tally_offset : nullptr;
+      long long* htally = tally_block(a, qh);
       flush_acc<MODE == kTallyTotals || MODE == kTallyAuto>(
           A, hscal, MODE == kTallyTotals || (MODE == kTallyAuto && !qh.per_tri), wave_tot);
       if (MODE == kTallyLane) flush_lane_tally(lt, htally, qh.nt);
@@ -940,7 +1025,7 @@ __global__ __launch_bounds__(kBlock) PROBE(__attribute__((amdgpu_waves_per_eu(ST
       held = j;
     }
     if (lane == 0) w_next_sh[wave] = p_begin;  // the next unclaimed particle of the wave's unit
-    long long* qtally = q.per_tri ? a.tally_base + q.tally_offset : nullptr;
+    long long* qtally = tally_block(a, q);
     const Node* nodes = uniform_ptr(q.nodes);
     const TriRec* tris = uniform_ptr(q.tris);
     const uint32_t* orig = uniform_ptr(q.orig);
@@ -989,8 +1074,8 @@ __global__ __launch_bounds__(kBlock) PROBE(__attribute__((amdgpu_waves_per_eu(ST
           bool limited = false;
           if (fin) out = finish_segment(tris, orig, q, L, s, h, fid, limited);
           count_pass(A, fin, out, h.valid, limited);
-          if (use_lds) tally<kTallyLds>(q, h, qtally, lt, q.nt, A);
-          else tally<MODE>(q, h, qtally, wave_tot, q.nt, A);
+          if (use_lds) tally<kTallyLds, STACK>(q, h, qtally, lt, stk, A);
+          else tally<MODE, STACK>(q, h, qtally, wave_tot, stk, A);
           if (fin) {
             if (out != kOutGoOn) {
               retire(q, L, A);
@@ -1197,17 +1282,22 @@ __global__ __launch_bounds__(kBlock) PROBE(__attribute__((amdgpu_waves_per_eu(ST
 // ---------------------------------------------------------------------------
 // a10: reduction and finalisation
 // ---------------------------------------------------------------------------
-constexpr int kReduceChunk = 4096;  // triangles per workgroup
+constexpr int kReduceChunk = 1024;  // triangles per workgroup
 
-__device__ __forceinline__ void reduce_one(const long long* __restrict__ tally, uint32_t nt, long long* __restrict__ scal,
-                                           uint32_t chunk) {
+// Sums of one query's triangles [chunk] over `copies` copies, `stride` words apart, into its totals.
+__device__ __forceinline__ void reduce_one(const long long* __restrict__ tally, uint32_t copies, uint64_t stride,
+                                           uint32_t nt, long long* __restrict__ scal, uint32_t chunk) {
   __shared__ long long part[kBlock / 64][7];
   long long s[7] = {0, 0, 0, 0, 0, 0, 0};
   const uint32_t t0 = chunk * kReduceChunk;
   const uint32_t t1 = t0 + kReduceChunk < nt ? t0 + kReduceChunk : nt;
-  for (uint32_t t = t0 + threadIdx.x; t < t1; t += kBlock)
+  // (triangle, copy) pairs over the lanes, so that small meshes with many copies use them all
+  const uint32_t items = (t1 - t0) * copies;
+  for (uint32_t i = threadIdx.x; i < items; i += kBlock) {
+    const uint32_t c = i / (t1 - t0), t = t0 + i % (t1 - t0);
 #pragma unroll
-    for (int c = 0; c < 7; ++c) s[c] += tally[7ull * t + c];
+    for (int k = 0; k < 7; ++k) s[k] += tally[c * stride + 7ull * t + k];
+  }
 #pragma unroll
   for (int c = 0; c < 7; ++c) s[c] = wave_sum(s[c]);
   if ((threadIdx.x & 63) == 0)
@@ -1223,15 +1313,28 @@ __device__ __forceinline__ void reduce_one(const long long* __restrict__ tally, 
 
 __global__ __launch_bounds__(kBlock) void reduce_kernel(const long long* __restrict__ tally, uint32_t nt,
                                                         long long* __restrict__ scal) {
-  reduce_one(tally, nt, scal, blockIdx.x);
+  reduce_one(tally, 1u, 0u, nt, scal, blockIdx.x);
 }
 
 __global__ __launch_bounds__(kBlock) void reduce_batch_kernel(const QueryDev* __restrict__ qs,
-                                                              long long* __restrict__ tally_base,
+                                                              long long* __restrict__ tally_base, TallyCopies copies,
                                                               long long* __restrict__ scal_base) {
   const QueryDev& q = qs[blockIdx.y];
   if (!q.per_tri || blockIdx.x * (uint32_t)kReduceChunk >= q.nt) return;
-  reduce_one(tally_base + q.tally_offset, q.nt, scal_base + q.scalar_offset, blockIdx.x);
+  const long long* const base = copies.base ? copies.base : tally_base;
+  reduce_one(base + q.tally_offset, copies.base ? 1u << copies.log2 : 1u, copies.stride, q.nt,
+             scal_base + q.scalar_offset, blockIdx.x);
+}
+
+__global__ __launch_bounds__(kBlock) void fold_tally_kernel(long long* __restrict__ tally, TallyCopies copies) {
+  for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < copies.stride; i += (uint64_t)gridDim.x * kBlock) {
+    long long v = 0;
+    for (uint32_t c = 0; c < (1u << copies.log2); ++c) {
+      v += copies.base[c * copies.stride + i];
+      copies.base[c * copies.stride + i] = 0;
+    }
+    tally[i] += v;
+  }
 }
 
 // F/q = K sum(w - w'), K = 2 Gamma_hat / (N S^2) (eq. drag with the effective
@@ -1534,10 +1637,14 @@ void launch_reduce(const long long* tally, uint32_t nt, long long* scal, hipStre
   reduce_kernel<<<g, kBlock, 0, st>>>(tally, nt, scal);
 }
 
-void launch_reduce_batch(const QueryDev* d_qs, uint32_t nq, long long* tally_base, long long* scal_base,
-                         uint32_t max_nt, hipStream_t st) {
+void launch_reduce_batch(const QueryDev* d_qs, uint32_t nq, long long* tally_base, const TallyCopies& copies,
+                         long long* scal_base, uint32_t max_nt, hipStream_t st) {
   dim3 g((max_nt + kReduceChunk - 1) / kReduceChunk, nq);
-  reduce_batch_kernel<<<g, kBlock, 0, st>>>(d_qs, tally_base, scal_base);
+  reduce_batch_kernel<<<g, kBlock, 0, st>>>(d_qs, tally_base, copies, scal_base);
+}
+
+void launch_fold_tally(long long* tally, const TallyCopies& copies, hipStream_t st) {
+  fold_tally_kernel<<<grid_for(copies.stride, 4096), kBlock, 0, st>>>(tally, copies);
 }
 
 void launch_finalize(const QueryDev* d_qs, const uint32_t* d_idx, const long long* scal_base, const ScalCopies& copies,
@@ -1552,7 +1659,7 @@ __global__ __launch_bounds__(kBlock) void reduce_slots_kernel(const QueryDev* __
                                                               long long* __restrict__ scal_base) {
   const QueryDev& q = qs[idx[blockIdx.y]];
   if (!q.per_tri || blockIdx.x * (uint32_t)kReduceChunk >= q.nt) return;
-  reduce_one(tally_base + q.tally_offset, q.nt, scal_base + q.scalar_offset, blockIdx.x);
+  reduce_one(tally_base + q.tally_offset, 1u, 0u, q.nt, scal_base + q.scalar_offset, blockIdx.x);
 }
 
 // Clears slots kFx..kCount of the listed per-triangle queries before a reduction.

@@ -25,6 +25,15 @@ struct ScalCopies {
   uint32_t log2;
 };
 
+// Copies of the per-triangle tallies: copy c of the words [0, stride) at
+// base + c * stride (base null: none).  Workgroup b adds into copy b % 2^log2;
+// the reduction sums them.
+struct TallyCopies {
+  long long* base;
+  uint32_t log2;
+  uint64_t stride;
+};
+
 struct TraceArgs {
   const Node* nodes;
   const TriRec* tris;
@@ -37,6 +46,7 @@ struct TraceArgs {
   long long* scal;            // [kScalarSlots]
   long long* copies;          // the query's ScalCopies (null: none), 1 + copy_mask of them
   uint32_t copy_mask;
+  TallyCopies tally_copies;   // base null or offset to the query
   int32_t* first_tri;         // optional, already offset to the query
   unsigned long long* counters;  // optional [2]: BVH nodes visited, triangle tests
   uint32_t nt;
@@ -64,6 +74,7 @@ struct BatchArgs {
   long long* tally_base;           // per-triangle tallies, indexed by QueryDev::tally_offset
   long long* scal_base;            // scalar blocks, indexed by QueryDev::scalar_offset
   ScalCopies copies;               // of the blocks of qs
+  TallyCopies tally_copies;        // of the words at tally_base
   uint32_t n_entries;
   uint32_t sub_log2;               // parts per entry (log2)
   uint32_t refill;                 // as TraceArgs::refill
@@ -85,7 +96,7 @@ struct BatchArgs {
 };
 
 // Word ranges cleared by one launch (n 0: none).
-constexpr int kClearRanges = 4;
+constexpr int kClearRanges = 5;
 struct ClearRanges {
   long long* p[kClearRanges];
   uint64_t n[kClearRanges];
@@ -146,7 +157,9 @@ uint64_t ceiling_valu_ops_per_lane(uint32_t iters);
 void launch_ceiling_read(const void* p, uint64_t bytes, uint32_t passes, int grid, hipStream_t st);
 void launch_ceiling_atomic(void* p, uint32_t slots, uint32_t per_thread, int grid, hipStream_t st);
 void launch_ceiling_lds_atomic(void* sink, uint32_t slots, uint32_t per_thread, int grid, hipStream_t st);
-void launch_reduce_batch(const QueryDev* d_qs, uint32_t nq, long long* tally_base, long long* scal_base,
-                         uint32_t max_nt, hipStream_t st);
+void launch_reduce_batch(const QueryDev* d_qs, uint32_t nq, long long* tally_base, const TallyCopies& copies,
+                         long long* scal_base, uint32_t max_nt, hipStream_t st);
+// tally[0, stride) += the copies, which are cleared.
+void launch_fold_tally(long long* tally, const TallyCopies& copies, hipStream_t st);
 
 }  // namespace tpmc
