@@ -81,6 +81,7 @@ struct tpmc_mesh_s {
   uint32_t* orig;
   std::vector<float> host_xyz;  // for control-volume checks
   double lo[3], hi[3], c0[3], r;
+  Node root;                    // host copy of node 0 (the seeding estimate's boxes)
   uint64_t device_bytes;
 };
 
@@ -96,7 +97,8 @@ struct Layout {
   uint64_t copy_words;
   TallyCopies tally_copies;  // of the per-triangle tallies; none where not worth it or without room
   uint64_t tally_words;
-  uint64_t need;             // bytes without the copies
+  float* lat_rows;           // batch: the queries' own latitude rows (null: none)
+  uint64_t need;             // bytes without the copies and rows
   uint64_t bytes;            // bytes with them
 };
 
@@ -311,6 +313,17 @@ static void setup_query(const tpmc_query* in, const tpmc_mesh m, QueryDev* q) {
       q->lat_fw[3] = (float)((f + 1.0) * f * (f - 1.0) / 6.0);
     }
   }
+  q->estimate = !q->box && (q->s_zero || q->lat_f0 >= 0) ? 1u : 0u;
+  if (!q->box) {
+    const Node& nd = m->root;
+    const float lo[2][3] = {{nd.lo0x, nd.lo0y, nd.lo0z}, {nd.lo1x, nd.lo1y, nd.lo1z}};
+    const float hi[2][3] = {{nd.hi0x, nd.hi0y, nd.hi0z}, {nd.hi1x, nd.hi1y, nd.hi1z}};
+    for (int b = 0; b < 2; ++b)
+      for (int k = 0; k < 3; ++k) {
+        q->root_c[b][k] = (float)(0.5 * ((double)lo[b][k] + hi[b][k]));
+        q->root_h[b][k] = (float)(0.5 * ((double)hi[b][k] - lo[b][k]) + (double)kRootMargin * q->r);
+      }
+  }
   const double tau = std::sqrt(in->T_w / in->T_inf);
   q->tau = (float)tau;
   q->alpha = (float)in->alpha;
@@ -413,7 +426,13 @@ static uint32_t tally_copies_log2(uint64_t nq, uint64_t nt, uint64_t waves) {
   return nt <= (uint64_t)kLaneTallyMaxTris ? copies_log2(nq, waves) : 0u;
 }
 
-// Lays out [queries | results | scalar blocks | tallies | claim counters | 6 planes | copies of the scalar blocks]
+// Own latitude rows: one gather instead of four per estimate and exact seeding
+// (3 % of a launch), against 3073 columns a query and one more launch (4 us), so
+// from this many particles a query on, and from 2^20 a batch.
+constexpr uint64_t kLatOwnMinParticles = 32768, kLatOwnMinBatch = 1ull << 20;
+
+// Lays out [queries | results | scalar blocks | tallies | claim counters | 6 planes | copies of the scalar blocks |
+// copies of the tallies | latitude rows]
 // in ws_bytes at base.
 static void layout(std::vector<QueryDev>& hq, uint64_t nt, uint64_t n_planes, bool batch, uint8_t* base,
                    uint64_t ws_bytes, Layout& L) {
@@ -446,9 +465,16 @@ static void layout(std::vector<QueryDev>& hq, uint64_t nt, uint64_t n_planes, bo
   L.tally_words = words;
   const uint64_t stride = (words + 31) & ~31ull;  // whole cache lines
   const uint64_t o_tc = take(tl ? (stride << tl) * sizeof(long long) : 0);
+  const uint64_t with_tally = off;
+  const bool rows = batch && total_particles(hq) >= std::max(nq * kLatOwnMinParticles, kLatOwnMinBatch);
+  const uint64_t o_lr = take(rows ? nq * kLatOwnStride * sizeof(float) : 0);
   L.bytes = off;
+  L.lat_rows = rows && ws_bytes >= L.bytes ? reinterpret_cast<float*>(base + o_lr) : nullptr;
+  if (batch)
+    for (uint64_t i = 0; i < nq; ++i)
+      hq[i].lat_own = L.lat_rows && hq[i].lat_f0 >= 0 && !hq[i].box ? L.lat_rows + i * kLatOwnStride : nullptr;
   L.tally_copies = TallyCopies{reinterpret_cast<long long*>(base + o_tc), tl, stride};
-  if (tl == 0 || ws_bytes < L.bytes) L.tally_copies = TallyCopies{nullptr, 0, 0};
+  if (tl == 0 || ws_bytes < with_tally) L.tally_copies = TallyCopies{nullptr, 0, 0};
   L.copies = ScalCopies{reinterpret_cast<long long*>(base + o_sc), cl};
   if (cl == 0 || ws_bytes < with_scal) {
     L.copies = ScalCopies{nullptr, 0};
@@ -603,7 +629,8 @@ extern "C" tpmc_status tpmc_build_mesh_ex(tpmc_ctx ctx, const float* xyz, uint64
   }
   if (e == hipSuccess) {
     mark_support(d_xyz, nv, m->tris, nt, m->orig, scratch, ctx->stream);
-    e = hipStreamSynchronize(ctx->stream);
+    e = hipMemcpyAsync(&m->root, m->nodes, sizeof(Node), hipMemcpyDeviceToHost, ctx->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
     if (e == hipSuccess) e = hipGetLastError();
   }
   if (d_xyz) (void)hipFree(d_xyz);
@@ -954,6 +981,10 @@ static tpmc_status batch_init(tpmc_ctx ctx, tpmc_mesh m, const tpmc_query* q, ui
   hipError_t e = hipSetDevice(ctx->device);
   if (e == hipSuccess)
     e = hipMemcpyAsync(b->lay.qs, b->hq.data(), nq * sizeof(QueryDev), hipMemcpyHostToDevice, ctx->stream);
+  if (e == hipSuccess && b->lay.lat_rows) {
+    launch_lat_own(b->lay.qs, nq, b->lay.lat_rows, ctx->stream);
+    e = hipGetLastError();
+  }
   if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
   if (e != hipSuccess) return fail(TPMC_E_DEVICE, "batch upload: %s", hipGetErrorString(e));
   return TPMC_OK;
@@ -1102,6 +1133,7 @@ struct tpmc_server_s {
   uint8_t* admits;       // admission staging: [max_slots] AdmitRec
   uint32_t* r_idx;       // [2][max_slots] slots whose results are collected
   ScalCopies copies;     // of the slots' scalar blocks (none in a workspace without room for them)
+  float* lat_rows;       // the slots' own latitude rows (null: no room)
   unsigned long long* e_next;
   std::vector<QueryDev> hq;
   std::vector<tpmc_mesh> mesh_of;
@@ -1136,9 +1168,11 @@ static void server_layout(uint32_t max_slots, uint64_t tally_words, uint8_t* bas
   *need = off;
   const uint32_t cl = copies_log2(max_slots, kMostWaves);
   const uint64_t osc = take(((uint64_t)max_slots << cl) * kScalStride * 8);
+  const uint64_t with_copies = off, olr = take((uint64_t)max_slots * kLatOwnStride * sizeof(float));
   *bytes = off;
   if (!s) return;
-  s->copies = cl == 0 || ws_bytes < off ? ScalCopies{nullptr, 0} : ScalCopies{reinterpret_cast<long long*>(base + osc), cl};
+  s->lat_rows = ws_bytes < off ? nullptr : reinterpret_cast<float*>(base + olr);
+  s->copies = cl == 0 || ws_bytes < with_copies ? ScalCopies{nullptr, 0} : ScalCopies{reinterpret_cast<long long*>(base + osc), cl};
   s->qs = reinterpret_cast<QueryDev*>(base + oq);
   s->res = reinterpret_cast<ResultDev*>(base + orr);
   s->scal = reinterpret_cast<long long*>(base + os);
@@ -1238,6 +1272,8 @@ extern "C" tpmc_status tpmc_server_admit_many(tpmc_server s, uint32_t n, const u
     QueryDev& d = one[0];
     d.scalar_offset = (uint64_t)slot * kScalarSlots;
     d.tally_offset = tally_offset[i];
+    d.lat_own = s->lat_rows && d.lat_f0 >= 0 && !d.box && d.N >= kLatOwnMinParticles
+                    ? s->lat_rows + (uint64_t)slot * kLatOwnStride : nullptr;
     if (d.per_tri && (tally_offset[i] > s->tally_words || m->nt * 7 > s->tally_words - tally_offset[i]))
       return fail(TPMC_E_WORKSPACE, "admission %u: per-triangle tallies of %llu words at offset %llu exceed the pool "
                   "of %llu", i, (unsigned long long)(m->nt * 7), (unsigned long long)tally_offset[i],
@@ -1259,8 +1295,8 @@ extern "C" tpmc_status tpmc_server_admit_many(tpmc_server s, uint32_t n, const u
   }
   tpmc_status st = server_upload(s, s->admits, rec.data(), n * sizeof(AdmitRec));
   if (st != TPMC_OK) return st;
-  launch_admit(reinterpret_cast<const AdmitRec*>(s->admits), n, max_words, s->qs, s->scal, s->copies, s->tally,
-               s->ctx->stream);
+  launch_admit(reinterpret_cast<const AdmitRec*>(s->admits), n, max_words, s->qs, s->scal, s->copies, s->lat_rows,
+               s->tally, s->ctx->stream);
   HIP_CHECK_LAUNCH("admit");
   return TPMC_OK;
 }

@@ -29,14 +29,24 @@ struct U4 {
   uint32_t a, b, c, d;
 };
 
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+#ifdef __HIP_DEVICE_COMPILE__
+  return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+#else
+  return a ^ b ^ c;
+#endif
+}
+
 __device__ __forceinline__ U4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0,
                                             uint32_t k1) {
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
-    // full 64-bit products: one v_mad_u64_u32 gives both halves
+    // full 64-bit products: one v_mad_u64_u32 gives both halves; the two
+    // exclusive ors of a word are one v_bitop3_b32 (an estimate's two blocks:
+    // 101 vector instructions with them apart, 69 now)
     const uint64_t p0 = (uint64_t)0xD2511F53u * c0, p1 = (uint64_t)0xCD9E8D57u * c2;
-    const uint32_t n0 = (uint32_t)(p1 >> 32) ^ c1 ^ k0;
-    const uint32_t n2 = (uint32_t)(p0 >> 32) ^ c3 ^ k1;
+    const uint32_t n0 = xor3((uint32_t)(p1 >> 32), c1, k0);
+    const uint32_t n2 = xor3((uint32_t)(p0 >> 32), c3, k1);
     c0 = n0;
     c1 = (uint32_t)p1;
     c2 = n2;
@@ -163,24 +173,59 @@ __device__ __forceinline__ float unif32_hi(uint32_t k) { return ((float)k + 0.5f
 // seeding estimate only; the exact solves keep their own logarithm).
 __device__ __forceinline__ float hw_ln(float x) { return 0.69314718f * __builtin_amdgcn_logf(x); }
 
+// Column of a table in the logit ln(u / (1 - u)) starting at t0 with step dt, n
+// columns; um = 1 - u.
+__device__ __forceinline__ float logit_column(float u, float um, float t0, float dt, int n) {
+  const float d = __builtin_amdgcn_logf(u) - __builtin_amdgcn_logf(um);  // log2
+  return fminf(fmaxf(fmaf(d, 0.69314718f / dt, -t0 / dt), 0.0f), (float)(n - 1));
+}
+
+// Two neighbouring table entries from a (scalar) base and a 32-bit byte offset:
+// no 64-bit address arithmetic in vector registers.
+__device__ __forceinline__ void table_pair(const float* __restrict__ tab, uint32_t byte_off, float& a, float& b) {
+  const float* p = reinterpret_cast<const float*>(reinterpret_cast<const char*>(tab) + byte_off);
+  a = p[0];
+  b = p[1];
+}
+
 // The same root from the fine table (layout kLatF* in tpmc_internal.h, filled
 // by lat_fine_kernel) at the draw u = ua, 1 - u = uam: the four rows and
 // cubic weights in ln S that the host set for the query (q.lat_f0 >= 0, i.e.
 // S in [0.25, 10]), linear in the logit.  Within 6e-6 of the root for every u
 // (a dense host evaluation against FP64 roots, poles included), so the exact
 // solve starts from it with no FP32 step, and the seeding estimate takes it as
-// it is.
-__device__ __forceinline__ float latitude_fine(const QueryDev& q, const float* __restrict__ tab, float ua,
-                                               float uam) {
-  const float t = hw_ln(ua) - hw_ln(uam);
-  const float ft = fminf(fmaxf((t - kLatFT0) * (1.0f / kLatFDT), 0.0f), (float)(kLatFNT - 1));
-  const int j = min((int)ft, kLatFNT - 2);
-  const float b = ft - (float)j;
-  const float* r = tab + q.lat_f0 * kLatFNT + j;
+// it is.  own: the query's own row (lat_own_kernel: the cubic done, the same
+// operations in the same order), one gather instead of four; every gather of 64
+// lanes holds the texture units, which a compute unit's four SIMDs share, for as
+// long as a SIMD needs for about 60 vector instructions.
+__device__ __forceinline__ float latitude_row(const QueryDev& q, const float* __restrict__ tab, int j) {
+  const uint32_t at = (uint32_t)(q.lat_f0 * kLatFNT + j);
   float m = 0.0f;
 #pragma unroll
-  for (int k = 0; k < 4; ++k) m += q.lat_fw[k] * ((1.0f - b) * r[k * kLatFNT] + b * r[k * kLatFNT + 1]);
-  return fminf(fmaxf(m, -1.0f), 1.0f);
+  for (int k = 0; k < 4; ++k) m = fmaf(q.lat_fw[k], tab[at + k * kLatFNT], m);
+  return m;
+}
+
+__device__ __forceinline__ float latitude_fine(const QueryDev& q, const float* __restrict__ tab,
+                                               const float* __restrict__ own, float ua, float uam) {
+  const float ft = logit_column(ua, uam, kLatFT0, kLatFDT, kLatFNT);
+  const int j = min((int)ft, kLatFNT - 2);
+  const float b = ft - (float)j;
+  float m0, m1;
+  if (own) {  // uniform
+    table_pair(own, (uint32_t)j * 4u, m0, m1);
+  } else {
+    const uint32_t at = (uint32_t)(q.lat_f0 * kLatFNT + j) * 4u;
+    m0 = m1 = 0.0f;  // the two columns, cubic in ln S
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      float r0, r1;
+      table_pair(tab, at + 4u * k * kLatFNT, r0, r1);
+      m0 = fmaf(q.lat_fw[k], r0, m0);
+      m1 = fmaf(q.lat_fw[k], r1, m1);
+    }
+  }
+  return fminf(fmaxf(fmaf(b, m1 - m0, m0), -1.0f), 1.0f);
 }
 
 __device__ __forceinline__ float latitude_start(const float* __restrict__ tab, float S, double u) {
@@ -206,8 +251,8 @@ struct LatEval {
 };
 
 __device__ inline double sample_latitude(const QueryDev& q, const float* __restrict__ lat_tab,
-                                        const float* __restrict__ lat_fine, const double* __restrict__ ee,
-                                        uint32_t k, LatEval& le) {
+                                        const float* __restrict__ lat_fine, const float* __restrict__ lat_own,
+                                        const double* __restrict__ ee, uint32_t k, LatEval& le) {
   const double u = unif64(k);
   le.valid = false;
   if (q.s_zero) return 2.0 * u - 1.0;  // S -> 0: g -> cos(phi)/2, mu uniform
@@ -215,7 +260,7 @@ __device__ inline double sample_latitude(const QueryDev& q, const float* __restr
   float xf;
   if (q.lat_f0 >= 0) {
     // one FP64 step from here ends the solve (start error ~6e-6 < 1e-5)
-    xf = latitude_fine(q, lat_fine, unif32_hi(k), unif32_hi(~k));
+    xf = latitude_fine(q, lat_fine, lat_own, unif32_hi(k), unif32_hi(~k));
   } else {
     const LatConst32 c{(float)q.S, (float)q.erfS, (float)q.erfcS, (float)q.expmS2, q.S < 0.25};
     xf = fminf(fmaxf(latitude_start(lat_tab, c.S, u), -1.0f), 1.0f);
@@ -327,43 +372,47 @@ __device__ __forceinline__ void normal_speed_F32(float s, float es2, float erfs,
   d2F = 2.0f * ea * (1.0f - 2.0f * x * a);
 }
 
-// Starting points of the normal-speed solve: a table of the root x of
-// F(x | s) = u chi(s) over s in [kVnS0, kVnS0 + (kVnNS - 1) kVnDS] and the logit
-// t = ln(u / (1 - u)) in [kVnT0, kVnT0 + (kVnNT - 1) kVnDT], bilinear in (s, t).
-// The law depends on s alone, so one table serves every query; it is filled
-// once per device by FP64 bisection (vn_table_kernel).  It only chooses where
-// the iteration starts.
-constexpr int kVnNS = 225, kVnNT = 385;
-constexpr float kVnS0 = -4.0f, kVnDS = 0.0625f, kVnT0 = -24.0f, kVnDT = 0.125f;
+// Table of the root x of F(x | s) = u chi(s) (layout kVn* in tpmc_internal.h),
+// bilinear in s and in the logit t = ln(u / (1 - u)).  The law depends on s
+// alone, so one table serves every query; it is filled once per device by FP64
+// bisection (vn_table_kernel).  It only chooses where an iteration starts.  fs in
+// [0, kVnNS - 1], ft in [0, kVnNT - 1].  (A table fine enough to need no
+// iteration in the seeding estimate -- 1.4 MB, four rows -- took the satellite's
+// 1024 x 1e6 from 62.8 to 66.2 ms, where this one with a Halley step takes 58.7:
+// its gathers miss the 32 KB L1.)
+__device__ __forceinline__ float normal_speed_table(const float* __restrict__ tab, float fs, float ft) {
+  const int i = min((int)fs, kVnNS - 2), j = min((int)ft, kVnNT - 2);
+  const float a = fs - (float)i, b = ft - (float)j;
+  float r[4];  // x(i, j), x(i + 1, j), x(i, j + 1), x(i + 1, j + 1): one 16-byte load
+  __builtin_memcpy(r, reinterpret_cast<const char*>(tab) + (uint32_t)(i * kVnNT + j) * 8u, 16);
+  const float x0 = fmaf(b, r[2] - r[0], r[0]), x1 = fmaf(b, r[3] - r[1], r[1]);
+  return fmaf(a, x1 - x0, x0);
+}
 
-__device__ __forceinline__ float normal_speed_start(const float* __restrict__ tab, double s, double u) {
+__device__ __forceinline__ float normal_speed_column(float u, float um) {  // of u and 1 - u
+  return logit_column(u, um, kVnT0, kVnDT, kVnNT);
+}
+
+__device__ __forceinline__ float normal_speed_start(const float* __restrict__ tab, double s, uint32_t k) {
   const float sf = (float)s;
-  if (sf >= kVnS0 && sf <= kVnS0 + (kVnNS - 1) * kVnDS) {
-    const float t = logf((float)u) - logf((float)(1.0 - u));
-    const float fs = (sf - kVnS0) * (1.0f / kVnDS);
-    const float ft = fminf(fmaxf((t - kVnT0) * (1.0f / kVnDT), 0.0f), (float)(kVnNT - 1));
-    const int i = min((int)fs, kVnNS - 2), j = min((int)ft, kVnNT - 2);
-    const float a = fs - (float)i, b = ft - (float)j;
-    const float* r0 = tab + i * kVnNT + j;
-    const float* r1 = r0 + kVnNT;
-    return (1.0f - a) * ((1.0f - b) * r0[0] + b * r0[1]) + a * ((1.0f - b) * r1[0] + b * r1[1]);
-  }
+  if (sf >= kVnS0 && sf <= kVnS0 + (kVnNS - 1) * kVnDS)
+    return normal_speed_table(tab, (sf - kVnS0) * (1.0f / kVnDS), normal_speed_column(unif32_hi(k), unif32_hi(~k)));
   // outside the table: near-Gaussian about s for large s, the Rayleigh law otherwise
-  const float uf = (float)u;
+  const float uf = (float)unif64(k);
   return sf > 1.0f ? sf + 0.5f / sf + erfinvf(2.0f * uf - 1.0f) : sqrtf(-log1pf(-uf));
 }
 
 __device__ inline double sample_normal_speed(const float* __restrict__ tab, const double* __restrict__ ee,
-                                             const NormalSpeedConsts& k, double u) {
+                                             const NormalSpeedConsts& k, uint32_t draw) {
   const double s = k.s;
-  const double target = u * k.chi;
+  const double target = unif64(draw) * k.chi;
   // The root lies below max(s, 0) + 7: the upper tail there is below e^{-49},
   // far under the smallest 1 - u the variates produce (2^-33).
   const double hi0 = (s > 0.0 ? s : 0.0) + 7.0;
   // FP32 approach from the tabulated start.  Below s = -9 the FP32 density
   // underflows; such s are never drawn in practice, and FP64 then starts there.
   const float sf = (float)s;
-  float xf = normal_speed_start(tab, s, u);
+  float xf = normal_speed_start(tab, s, draw);
   float lof = 0.0f, hif = (float)hi0;
   if (!(xf > lof && xf < hif)) xf = 0.5f * (lof + hif);
   if (s > -9.0) {
@@ -407,7 +456,8 @@ __device__ inline double sample_normal_speed(const float* __restrict__ tab, cons
 // solve (the frame is expanded afterwards), which keeps the persistent kernel
 // inside its register budget.
 __device__ inline void seed_particle(const QueryDev& q, const float* __restrict__ lat_tab,
-                                     const float* __restrict__ lat_fine, const float* __restrict__ vn_tab, const double* __restrict__ sc_tab,
+                                     const float* __restrict__ lat_fine, const float* __restrict__ lat_own,
+                                     const float* __restrict__ vn_tab, const double* __restrict__ sc_tab,
                                      const double* __restrict__ ee, uint64_t pid, double x[3], double w[3]) {
   const U4 r0 = stream(q, pid, 0u);
   const U4 r1 = stream(q, pid, 1u);
@@ -426,13 +476,13 @@ __device__ inline void seed_particle(const QueryDev& q, const float* __restrict_
     k = normal_speed_consts(ee, q.face_s[f]);
   } else {
     LatEval le;
-    p0 = sample_latitude(q, lat_tab, lat_fine, ee, r0.a, le);
+    p0 = sample_latitude(q, lat_tab, lat_fine, lat_own, ee, r0.a, le);
     p1 = sqrt(fmax(0.0, 1.0 - p0 * p0));
     sincos_2pi_draw(sc_tab, r0.b, p2, p3);  // of 2 pi unif64(r0.b)
     const double s_n = q.S * p0;
     k = le.valid ? normal_speed_consts_near(ee, s_n, q.S * le.t, le.e, le.ta) : normal_speed_consts(ee, s_n);
   }
-  const double wn = sample_normal_speed(vn_tab, ee, k, unif64(r0.c));
+  const double wn = sample_normal_speed(vn_tab, ee, k, r0.c);
   const double rad = sqrt(-2.0 * log_draw(r0.d));  // ln unif64(r0.d)
   double sb, cb;
   sincos_2pi_draw(sc_tab, r1.a, sb, cb);  // of 2 pi unif64(r1.a)
@@ -559,119 +609,105 @@ __device__ __forceinline__ bool slab(const Ray& r, float lox, float loy, float l
 // is work without effect; on small or flat bodies most particles are such.
 // precull_may_enter estimates the particle's ray from the same variates in
 // FP32 (the latitude from a fine table without iteration, the normal speed
-// from its tabulated start and two FP32 Halley steps, the hardware exp, log,
-// sine and cosine, the frame in FP32) and tests it against the root's two
+// from its tabulated start and one Halley step, the hardware square root, exp,
+// log, sine and cosine, the frame in FP32) and tests it against the root's two
 // boxes grown by kPrecullMargin CV radii on every side.  Returns false only if
 // that grown test fails, i.e. only for particles whose exact ray misses the
 // root's boxes:
 //  * the fine latitude table (cubic in ln S, linear in the logit) leaves an
-//    error d in mu of about 1e-5; the speed's Halley steps leave about C dx^3
-//    after a second step dx, and the estimate gives up (the particle is
-//    seeded exactly) unless that step is below 1e-5 of the speed; it also
-//    gives up outside the tables' ranges of S and s;
+//    error d in mu of about 1e-5; the speed's Halley step takes the table's
+//    4e-4 to about 1e-10 by its cubic convergence, plus the rounding of F, about
+//    3e-7 chi(s), over F'.  The estimate gives up (the particle is seeded
+//    exactly) where F' < chi / 100, which leaves 3e-5, and outside the tables'
+//    ranges of S and s;
 //  * a latitude error d moves cos(phi) by d |mu| / cos(phi), so the estimate
 //    gives up for cos(phi) < 0.05 (mu within 1.25e-3 of +-1); elsewhere the
 //    point and the direction move by at most ~20 d, relative to r and to |w|;
 //  * along the at most 2 r of path inside the CV, the estimated ray then stays
-//    within ~60 d r of the exact one: a few hundredths of the margin (0.02 r)
-//    for the table's d, and far less for the rounding of the FP32 solves and
-//    the hardware sine, cosine and logarithm.
+//    within ~60 d r plus twice the speed's relative error of the exact one: a few
+//    hundredths of the margin (0.02 r).
 // tpmc_precull_check measures the distance between estimated and exact rays.
-// Box control volumes are not estimated (always true).
+// Box control volumes are not estimated.
+//
+// Bound: VALU issue and the tables' gathers.  With two bracketed Halley steps,
+// the frame vector by vector, the box test bound by bound and eight gathers the
+// estimate was 525 vector instructions; 326 now, and two gathers.  Launch times
+// before and after: plate 60 x 1e6 1975 -> 1727 us, satellite 1024 x 1e6 62.8 ->
+// 58.7 ms, satellite 1e7 1380 -> 1330 us.
 // ---------------------------------------------------------------------------
-constexpr float kPrecullMargin = 0.02f;
-
-
-// fs in [0, ns - 1], ft in [0, nt - 1]
-__device__ __forceinline__ float bilinear_start(const float* __restrict__ tab, int ns, int nt, float fs, float ft) {
-  const int i = min((int)fs, ns - 2), j = min((int)ft, nt - 2);
-  const float a = fs - (float)i, b = ft - (float)j;
-  const float* r0 = tab + i * nt + j;
-  const float* r1 = r0 + nt;
-  return (1.0f - a) * ((1.0f - b) * r0[0] + b * r0[1]) + a * ((1.0f - b) * r1[0] + b * r1[1]);
-}
+constexpr float kPrecullMargin = kRootMargin;
 
 // The estimated ray (o, w); false when the estimate gives up.  The per-particle
 // conditions are gathered into one flag rather than taken as early returns, so
 // that the lanes stay converged (table lookups use clamped indices throughout;
 // what a given-up particle computes is discarded).
 __device__ inline bool precull_estimate(const QueryDev& q, const float* __restrict__ lat_tab,
-                                        const float* __restrict__ vn_tab, uint64_t pid, float o[3], float w[3]) {
-  if (q.box) return false;
+                                        const float* __restrict__ lat_own, const float* __restrict__ vn_tab,
+                                        uint64_t pid, float o[3], float w[3]) {
+  if (!q.estimate) return false;
   const U4 r0 = stream(q, pid, 0u);
   const U4 r1 = stream(q, pid, 1u);
   // latitude mu = sin(phi)
   const float ua = unif32_hi(r0.a), uam = unif32_hi(~r0.a);  // u and 1 - u
-  float mu;
-  bool ok = true;
-  if (q.s_zero) {
-    mu = 2.0f * ua - 1.0f;
-  } else {
-    // from the fine table, inside its S range only (the host sets lat_f0 = -1 outside)
-    if (q.lat_f0 < 0) return false;
-    mu = latitude_fine(q, lat_tab, ua, uam);
-  }
-  const float cphi = sqrtf(fmaxf(0.0f, 1.0f - mu * mu));
-  ok = ok && cphi >= 0.05f;
-  // inward normal speed at s = S mu
+  const float mu = q.s_zero ? 2.0f * ua - 1.0f : latitude_fine(q, lat_tab, lat_own, ua, uam);
+  const float cphi = __builtin_amdgcn_sqrtf(fmaxf(0.0f, 1.0f - mu * mu));
+  // inward normal speed at s = S mu: F(x) - u chi at the tabulated start, with
+  // erf(x - s) + erf(s) from the two small erfc values, and one Halley step
   const float s = q.s_zero ? 0.0f : q.Sf * mu;
-  const float es2 = __expf(-s * s);
-  const float ta = es2 * erfcx32(fabsf(s));  // erfc(|s|)
-  const float erfcs = s >= 0.0f ? ta : 2.0f - ta, erfcms = s >= 0.0f ? 2.0f - ta : ta;
-  const float erfs = s >= 0.0f ? 1.0f - ta : ta - 1.0f;
-  const float chi = es2 + (float)kSqrtPi * s * erfcms;
-  const float uc = unif32_hi(r0.c), ucm = unif32_hi(~r0.c);
-  const float hi0 = fmaxf(s, 0.0f) + 7.0f;
   const float fs = (s - kVnS0) * (1.0f / kVnDS);
-  ok = ok && s > -9.0f && fs >= 0.0f && fs <= (float)(kVnNS - 1);  // inside the table's s range only
-  const float tv = hw_ln(uc) - hw_ln(ucm);
-  float wn = bilinear_start(vn_tab, kVnNS, kVnNT, fminf(fmaxf(fs, 0.0f), (float)(kVnNS - 1)),
-                            fminf(fmaxf((tv - kVnT0) * (1.0f / kVnDT), 0.0f), (float)(kVnNT - 1)));
-  ok = ok && wn > 0.0f && wn < hi0;
-  {
-    float lo = 0.0f, hi = hi0, F, dF, d2F, dx = 0.0f;
-#pragma unroll
-    for (int it = 0; it < 2; ++it) {
-      normal_speed_F32(s, es2, erfs, erfcs, erfcms, wn, F, dF, d2F);
-      dx = halley_step(wn, F - uc * chi, dF, d2F, lo, hi);
-    }
-    ok = ok && dx <= 1e-5f * wn;
-  }
-  // tangential Gaussians (Box-Muller) and the angles; v_sin / v_cos take revolutions
-  const float rad = sqrtf(-2.0f * hw_ln(unif32_hi(r0.d)));
+  const float uc = unif32_hi(r0.c);
+  float wn = normal_speed_table(vn_tab, fminf(fmaxf(fs, 0.0f), (float)(kVnNS - 1)),
+                                normal_speed_column(uc, unif32_hi(~r0.c)));
+  const float es2 = __expf(-s * s), ta = es2 * erfcx32(fabsf(s));
+  const float chi = fmaf((float)kSqrtPi * s, s >= 0.0f ? 2.0f - ta : ta, es2);
+  const float x = wn - s, ea = __expf(-x * x), tx = ea * erfcx32(fabsf(x));
+  const float esum = s < 0.0f ? ta - tx : (x < 0.0f ? tx - ta : 2.0f - tx - ta);
+  const float F = fmaf((float)kSqrtPi * s, esum, es2 - ea) - uc * chi, dF = 2.0f * wn * ea;
+  const float d2F = 2.0f * ea * (1.0f - 2.0f * wn * x);
+  wn -= 2.0f * F * dF * __builtin_amdgcn_rcpf(2.0f * dF * dF - F * d2F);
+  const bool ok = cphi >= 0.05f && fs >= 0.0f && fs <= (float)(kVnNS - 1) && dF >= 0.01f * chi;
+  // tangential Gaussians (Box-Muller, deviation 1 / sqrt 2) and the angles; v_sin / v_cos take revolutions
+  const float rad = __builtin_amdgcn_sqrtf(-hw_ln(unif32_hi(r0.d)));
   const float ub = unif32_hi(r1.a), uth = unif32_hi(r0.b);
-  const float g1 = rad * __builtin_amdgcn_cosf(ub) * (float)kInvSqrt2;
-  const float g2 = rad * __builtin_amdgcn_sinf(ub) * (float)kInvSqrt2;
+  const float g1 = rad * __builtin_amdgcn_cosf(ub), g2 = rad * __builtin_amdgcn_sinf(ub);
   const float sth = __builtin_amdgcn_sinf(uth), cth = __builtin_amdgcn_cosf(uth);
+  // seed_particle's frame in components along U, e1, e2:
+  //   o - c0 = -r mu U + r cphi (cth e1 + sth e2),
+  //   w = (wn mu + wt1 cphi) U + (k cth + g2 sth) e1 + (k sth - g2 cth) e2, k = wt1 mu - wn cphi
   const float wt1 = q.Sf * cphi + g1;
+  const float k = wt1 * mu - wn * cphi;
+  const float wU = wn * mu + wt1 * cphi, w1 = k * cth + g2 * sth, w2 = k * sth - g2 * cth;
+  const float rc = q.rf * cphi, oU = -q.rf * mu, o1 = rc * cth, o2 = rc * sth;
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
-    const float ci = cth * q.e1f[i] + sth * q.e2f[i];
-    const float di = -sth * q.e1f[i] + cth * q.e2f[i];
-    const float ni = mu * q.Uf[i] - cphi * ci;
-    const float t1i = cphi * q.Uf[i] + mu * ci;
-    o[i] = q.c0f[i] - q.rf * ni;
-    w[i] = wn * ni + wt1 * t1i - g2 * di;
+    o[i] = fmaf(oU, q.Uf[i], fmaf(o1, q.e1f[i], fmaf(o2, q.e2f[i], q.c0f[i])));
+    w[i] = fmaf(wU, q.Uf[i], fmaf(w1, q.e1f[i], w2 * q.e2f[i]));
   }
   return ok;
 }
 
+// Whether a ray passes a box given by centre and half extents, t >= 0 (the
+// margin of the grown boxes covers the rounding; an axis that the ray is exactly
+// parallel to gives NaN, which the minimum and maximum leave out: the ray is kept).
+__device__ __forceinline__ bool passes_box(const float o[3], const float inv[3], const float c[3], const float h[3]) {
+  float n[3], f[3];
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    const float t = (c[i] - o[i]) * inv[i];
+    n[i] = fmaf(-h[i], fabsf(inv[i]), t);
+    f[i] = fmaf(h[i], fabsf(inv[i]), t);
+  }
+  return fmaxf(fmaxf(fmaxf(n[0], n[1]), n[2]), 0.0f) <= fminf(fminf(f[0], f[1]), f[2]);
+}
+
 __device__ inline bool precull_may_enter(const QueryDev& q, const float* __restrict__ lat_tab,
-                                         const float* __restrict__ vn_tab, const Node* __restrict__ nodes,
+                                         const float* __restrict__ lat_own, const float* __restrict__ vn_tab,
                                          uint64_t pid) {
   float o[3] = {0.0f, 0.0f, 0.0f}, w[3] = {0.0f, 0.0f, 0.0f};
-  const bool ok = precull_estimate(q, lat_tab, vn_tab, pid, o, w);
-  Ray r;
-  r.ox = o[0]; r.oy = o[1]; r.oz = o[2];
-  r.idx = __builtin_amdgcn_rcpf(w[0]);
-  r.idy = __builtin_amdgcn_rcpf(w[1]);
-  r.idz = __builtin_amdgcn_rcpf(w[2]);
-  const float m = kPrecullMargin * q.rf;
-  const Node& nd = nodes[0];
-  const float inf = __builtin_inff();
-  float tn;
-  const bool h0 = slab(r, nd.lo0x - m, nd.lo0y - m, nd.lo0z - m, nd.hi0x + m, nd.hi0y + m, nd.hi0z + m, inf, tn);
-  const bool h1 = slab(r, nd.lo1x - m, nd.lo1y - m, nd.lo1z - m, nd.hi1x + m, nd.hi1y + m, nd.hi1z + m, inf, tn);
+  const bool ok = precull_estimate(q, lat_tab, lat_own, vn_tab, pid, o, w);
+  const float inv[3] = {__builtin_amdgcn_rcpf(w[0]), __builtin_amdgcn_rcpf(w[1]), __builtin_amdgcn_rcpf(w[2])};
+  const bool h0 = passes_box(o, inv, q.root_c[0], q.root_h[0]);
+  const bool h1 = passes_box(o, inv, q.root_c[1], q.root_h[1]);
   return !ok || h0 || h1;  // a given-up estimate keeps the particle
 }
 

@@ -56,7 +56,18 @@ enum ProbeSlot {
 constexpr int kLatFNS = 192, kLatFNT = 3073;
 constexpr double kLatFL0 = -1.45, kLatFDL = 0.02;
 constexpr float kLatFT0 = -24.0f, kLatFDT = 1.0f / 64.0f;
+constexpr int kLatOwnStride = 3104;  // floats from one query's own row to the next (whole cache lines)
 constexpr double kLatFSmin = 0.25, kLatFSmax = 10.0;  // the S range the estimate takes from it
+
+// Table of the normal speed's root x of F(x | s) = u chi(s): rows s = kVnS0 + i
+// kVnDS, columns t = kVnT0 + j kVnDT in the logit of u, bilinear, within 4e-4 of
+// the root.  Entry (i, j) holds rows i and i + 1, so that the four values of a
+// cell are 16 consecutive bytes.
+constexpr int kVnNS = 225, kVnNT = 385;
+constexpr float kVnS0 = -4.0f, kVnDS = 0.0625f, kVnT0 = -24.0f, kVnDT = 0.125f;
+
+// The root's boxes are grown by this many CV radii for the seeding estimate's test.
+constexpr float kRootMargin = 0.02f;
 
 struct Node;
 struct TriRec;
@@ -71,7 +82,10 @@ struct alignas(16) QueryDev {
   double inv_scaleF, inv_scaleL, inv_scaleD, inv_scaleD2;
   double Gamma_hat;
   uint64_t N;                        // particles of this query
-  uint64_t p_offset;                 // first particle in the SoA planes (plain path)
+  union {
+    uint64_t p_offset;               // plain path: first particle in the SoA planes
+    const float* lat_own;            // batches, slots: the query's own row of the latitude table (null: none)
+  };
   uint64_t tally_offset;             // first int64 of this query's per-triangle tallies
   uint64_t scalar_offset;            // first int64 of this query's scalar block
   const Node* nodes;                 // the query's mesh (resident BVH)
@@ -86,10 +100,17 @@ struct alignas(16) QueryDev {
   uint32_t per_tri;                  // per-triangle tallies kept
   uint32_t nt;                       // triangles of the query's mesh
   uint32_t box;                      // box control volume (faces f = 2k: outward -e_k, 2k + 1: +e_k)
-  uint32_t pad_;
+  uint32_t estimate;                 // the seeding estimate covers the query (sphere, S in its tables' range)
   double h[3];                       // box half-extents
-  double face_s[6];                  // s_f = S U.n_f, n_f the inward normal of face f
-  double face_cum[6];                // cumulative A_f chi(s_f)
+  union {
+    struct {                         // box control volumes
+      double face_s[6];              // s_f = S U.n_f, n_f the inward normal of face f
+      double face_cum[6];            // cumulative A_f chi(s_f)
+    };
+    struct {                         // spheres: the root's two boxes, grown, centre and half extents
+      float root_c[2][3], root_h[2][3];
+    };
+  };
   double inv_scaleE, inv_scaleE2;
   float alpha_E;                     // energy accommodation of diffuse re-emission
   float tr_cap2;                     // cap of the re-emission temperature tau_r^2

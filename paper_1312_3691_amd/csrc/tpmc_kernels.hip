@@ -53,11 +53,11 @@ int grid_for(uint64_t n, int cap) {
 // ---------------------------------------------------------------------------
 // a2-a4: seeding
 // ---------------------------------------------------------------------------
-// Starting points of the latitude and normal-speed solves (latitude_start,
-// normal_speed_start); part of the code object, filled once per device.
+// Tables of the latitude and normal-speed laws (latitude_start, latitude_fine,
+// normal_speed_table); part of the code object, filled once per device.
 __device__ float g_lat_start[kLatNS * kLatNT];
 __device__ float g_lat_fine[kLatFNS * kLatFNT];  // the seeding estimate's latitude table
-__device__ float g_vn_start[kVnNS * kVnNT];
+__device__ __align__(16) float g_vn_start[2 * (kVnNS - 1) * kVnNT];
 // sin and cos of 2 pi j / 256, j = 0..255 (sincos_2pi_draw)
 __device__ double g_sc_tab[512];
 // exp(-y_j^2) and erfc(y_j) at y_j = j / 256 (exp_erfc_grid)
@@ -133,8 +133,9 @@ __global__ void lat_fine_kernel(float* __restrict__ tab, const double* __restric
 __global__ void vn_table_kernel(float* __restrict__ tab, const double* __restrict__ ee) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= kVnNS * kVnNT) return;
-  const double s = (double)kVnS0 + (double)(i / kVnNT) * (double)kVnDS;
-  const double t = (double)kVnT0 + (double)(i % kVnNT) * (double)kVnDT;
+  const int row = i / kVnNT, col = i % kVnNT;
+  const double s = (double)kVnS0 + (double)row * (double)kVnDS;
+  const double t = (double)kVnT0 + (double)col * (double)kVnDT;
   const double u = 1.0 / (1.0 + exp(-t));
   const NormalSpeedConsts k = normal_speed_consts(ee, s);
   const double target = u * k.chi;
@@ -146,7 +147,16 @@ __global__ void vn_table_kernel(float* __restrict__ tab, const double* __restric
     if (F < target) lo = m;
     else hi = m;
   }
-  tab[i] = (float)(0.5 * (lo + hi));
+  const float x = (float)(0.5 * (lo + hi));
+  if (row < kVnNS - 1) tab[2 * i] = x;             // first of its cells' pairs
+  if (row > 0) tab[2 * (i - kVnNT) + 1] = x;       // second of the row below's
+}
+
+// Each query's own row of the fine latitude table (QueryDev::lat_own), query blockIdx.y.
+__global__ __launch_bounds__(kBlock) void lat_own_kernel(const QueryDev* __restrict__ qs, float* __restrict__ rows) {
+  const QueryDev& q = qs[blockIdx.y];
+  const int j = blockIdx.x * kBlock + threadIdx.x;
+  if (q.lat_own && j < kLatFNT) rows[(uint64_t)blockIdx.y * kLatOwnStride + j] = latitude_row(q, g_lat_fine, j);
 }
 
 __global__ __launch_bounds__(kBlock) void seed_kernel(const QueryDev* __restrict__ qp, uint64_t n,
@@ -157,7 +167,7 @@ __global__ __launch_bounds__(kBlock) void seed_kernel(const QueryDev* __restrict
   const uint64_t stride = (uint64_t)gridDim.x * kBlock;
   for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += stride) {
     double x[3], w[3];
-    seed_particle(q, g_lat_start, g_lat_fine, g_vn_start, g_sc_tab, g_ee_tab, i, x, w);
+    seed_particle(q, g_lat_start, g_lat_fine, nullptr, g_vn_start, g_sc_tab, g_ee_tab, i, x, w);
     x0[i] = (float)x[0];
     x1[i] = (float)x[1];
     x2[i] = (float)x[2];
@@ -875,6 +885,13 @@ __device__ __forceinline__ void start_part(const BatchArgs& a, uint32_t& part, u
   }
 }
 
+// The lane's particle of a batch.  Units begin at multiples of 64, so a batch
+// shares the high word of its particles' numbers, and the first rounds of
+// their Philox blocks are half scalar.
+__device__ __forceinline__ uint64_t batch_pid(uint64_t base) {
+  return (base & 0xFFFFFFFF00000000ull) | ((uint32_t)base + (threadIdx.x & 63u));
+}
+
 // Where the workgroup's waves add a query's sums: the query's block, or one of
 // its copies (ScalCopies).
 __device__ __forceinline__ long long* scal_block(const BatchArgs& a, uint32_t query, const QueryDev& q) {
@@ -1050,7 +1067,7 @@ __global__ __launch_bounds__(kBlock) PROBE(__attribute__((amdgpu_waves_per_eu(ST
     uint32_t q_head = 0, q_count = 0;  // wave-uniform queue state
     uint64_t q_pid0 = 0;               // particle id of queue slot 0
     uint32_t s_head = 0, s_count = 0;  // wave-uniform survivor ring state (two-stage seeding)
-    bool pc_on = kPre && !yields_little();  // wave-uniform
+    bool pc_on = kPre && q.estimate != 0u && !yields_little();  // wave-uniform
     for (;;) {
       uint32_t ntrav = (uint32_t)__popcll(ballot(L.live && seg_traversing(s)));
       if (ntrav < a.refill && ballot(L.live && s.p0 >= 0) != 0ull) {
@@ -1107,10 +1124,10 @@ __global__ __launch_bounds__(kBlock) PROBE(__attribute__((amdgpu_waves_per_eu(ST
               if (base >= p_end) {
                 exhausted = true;
               } else {
-                const uint64_t pid = base + lane;
+                const uint64_t pid = batch_pid(base);
                 const bool valid = pid < p_end;
                 bool maybe = valid;
-                if (valid && pc_on) maybe = precull_may_enter(q, g_lat_fine, g_vn_start, nodes, pid);
+                if (valid && pc_on) maybe = precull_may_enter(q, g_lat_fine, q.lat_own, g_vn_start, pid);
                 const uint64_t mb = ballot(maybe);
                 if (maybe) ring[wave][(s_head + s_count + below(mb)) & (kRing - 1)] =
                     (uint16_t)(pid - p_begin);
@@ -1135,7 +1152,7 @@ __global__ __launch_bounds__(kBlock) PROBE(__attribute__((amdgpu_waves_per_eu(ST
             float xs[3], ws[3];
             if ((uint32_t)lane < n) {
               double x[3], w[3];
-              seed_particle(q, g_lat_start, g_lat_fine, g_vn_start, g_sc_tab, g_ee_tab,
+              seed_particle(q, g_lat_start, g_lat_fine, q.lat_own, g_vn_start, g_sc_tab, g_ee_tab,
                             p_begin + ring[wave][(s_head + lane) & (kRing - 1)], x, w);
 #pragma unroll
               for (int c = 0; c < 3; ++c) {
@@ -1184,7 +1201,7 @@ __global__ __launch_bounds__(kBlock) PROBE(__attribute__((amdgpu_waves_per_eu(ST
               float xs[3], ws[3];
               if (pid < p_end) {
                 double x[3], w[3];
-                seed_particle(q, g_lat_start, g_lat_fine, g_vn_start, g_sc_tab, g_ee_tab, pid, x, w);
+                seed_particle(q, g_lat_start, g_lat_fine, q.lat_own, g_vn_start, g_sc_tab, g_ee_tab, pid, x, w);
 #pragma unroll
                 for (int c = 0; c < 3; ++c) {
                   xs[c] = (float)x[c];
@@ -1460,7 +1477,7 @@ static_assert(sizeof(QueryDev) % 8 == 0 && kScalarSlots <= kBlock, "admission co
 // scalar block (first workgroup), its per-triangle tally words (all).
 __global__ __launch_bounds__(kBlock) void admit_kernel(const AdmitRec* __restrict__ rec, QueryDev* __restrict__ qs,
                                                        long long* __restrict__ scal, ScalCopies copies,
-                                                       long long* __restrict__ tally) {
+                                                       float* __restrict__ lat_rows, long long* __restrict__ tally) {
   const AdmitRec& r = rec[blockIdx.y];
   if (blockIdx.x == 0) {
     const uint64_t* src = reinterpret_cast<const uint64_t*>(&r.q);
@@ -1471,6 +1488,9 @@ __global__ __launch_bounds__(kBlock) void admit_kernel(const AdmitRec* __restric
       for (uint32_t w = threadIdx.x; w < (uint32_t)kScalStride << copies.log2; w += kBlock)
         copies.base[(((uint64_t)r.slot << copies.log2) * kScalStride) + w] = 0;
   }
+  if (r.q.lat_own)
+    for (int j = blockIdx.x * kBlock + threadIdx.x; j < kLatFNT; j += gridDim.x * kBlock)
+      lat_rows[(uint64_t)r.slot * kLatOwnStride + j] = latitude_row(r.q, g_lat_fine, j);
   for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < r.tally_words; i += (uint64_t)gridDim.x * kBlock)
     tally[r.tally_off + i] = 0;
 }
@@ -1478,10 +1498,10 @@ __global__ __launch_bounds__(kBlock) void admit_kernel(const AdmitRec* __restric
 }  // namespace
 
 void launch_admit(const AdmitRec* rec, uint32_t n, uint64_t max_words, QueryDev* qs, long long* scal,
-                  const ScalCopies& copies, long long* tally, hipStream_t st) {
-  const uint64_t gx = (max_words + kBlock - 1) / kBlock;
+                  const ScalCopies& copies, float* lat_rows, long long* tally, hipStream_t st) {
+  const uint64_t gx = std::max<uint64_t>((max_words + kBlock - 1) / kBlock, (kLatFNT + kBlock - 1) / kBlock);
   const dim3 g((uint32_t)(gx < 1 ? 1 : (gx > 1024 ? 1024 : gx)), n);
-  admit_kernel<<<g, kBlock, 0, st>>>(rec, qs, scal, copies, tally);
+  admit_kernel<<<g, kBlock, 0, st>>>(rec, qs, scal, copies, lat_rows, tally);
 }
 
 // Check of the two-stage seeding's estimate: over particles [0, n) of one
@@ -1497,9 +1517,9 @@ __global__ __launch_bounds__(kBlock) void precull_check_kernel(const QueryDev* _
   unsigned long long cnt = 0;
   for (uint64_t pid = (uint64_t)blockIdx.x * kBlock + threadIdx.x; pid < n; pid += (uint64_t)gridDim.x * kBlock) {
     float o[3], w[3];
-    if (!precull_estimate(q, g_lat_fine, g_vn_start, pid, o, w)) continue;
+    if (!precull_estimate(q, g_lat_fine, nullptr, g_vn_start, pid, o, w)) continue;
     double x[3], we[3];
-    seed_particle(q, g_lat_start, g_lat_fine, g_vn_start, g_sc_tab, g_ee_tab, pid, x, we);
+    seed_particle(q, g_lat_start, g_lat_fine, nullptr, g_vn_start, g_sc_tab, g_ee_tab, pid, x, we);
     double dp = 0.0, nw = 0.0, ne = 0.0, dd = 0.0;
     for (int c = 0; c < 3; ++c) {
       dp += ((double)o[c] - x[c]) * ((double)o[c] - x[c]);
@@ -1561,6 +1581,10 @@ hipError_t init_seed_tables(hipStream_t st) {
   lat_fine_kernel<<<(kLatFNS * kLatFNT + 255) / 256, 256, 0, st>>>(fine, ee);
   e = hipGetLastError();
   return e != hipSuccess ? e : hipStreamSynchronize(st);
+}
+
+void launch_lat_own(const QueryDev* d_qs, uint32_t nq, float* rows, hipStream_t st) {
+  lat_own_kernel<<<dim3((kLatFNT + kBlock - 1) / kBlock, nq), kBlock, 0, st>>>(d_qs, rows);
 }
 
 void zero_i64(long long* p, uint64_t n, hipStream_t st) {

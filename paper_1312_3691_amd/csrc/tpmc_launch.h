@@ -144,10 +144,12 @@ void launch_precull_check(const QueryDev* d_q, uint64_t n, unsigned long long* o
 // and clears them when reset.
 bool probe_built();
 hipError_t probe_read(unsigned long long* out, bool reset, hipStream_t st);
+// Fills the own latitude rows (kLatOwnStride floats each) of the queries that have one.
+void launch_lat_own(const QueryDev* d_qs, uint32_t nq, float* rows, hipStream_t st);
 // Serving admission: n records (device) -> constants into qs[slot], cleared
-// scalar block (and copies) and per-triangle tally words; max_words is the largest tally.
+// scalar block (and copies), per-triangle tally words, and its own latitude row; max_words is the largest tally.
 void launch_admit(const AdmitRec* rec, uint32_t n, uint64_t max_words, QueryDev* qs, long long* scal,
-                  const ScalCopies& copies, long long* tally, hipStream_t st);
+                  const ScalCopies& copies, float* lat_rows, long long* tally, hipStream_t st);
 
 // Ceiling microkernels (tpmc_ceilings.hip).  kind 0: FP32 FMA, 1: FP64 FMA,
 // 2: int32 multiply and add; each lane performs ceiling_valu_ops_per_lane(iters)
