@@ -402,6 +402,13 @@ static tpmc_status make_queries(tpmc_mesh m, const tpmc_query* q, uint32_t nq, s
 // ---------------------------------------------------------------------------
 static uint64_t align256(uint64_t v) { return (v + 255) & ~255ull; }
 
+// Particles of the largest of queries [i, i + n).
+static uint64_t most_particles(const std::vector<QueryDev>& hq, uint32_t i, uint32_t n) {
+  uint64_t most = 0;
+  for (uint32_t k = i; k < i + n; ++k) most = std::max(most, hq[k].N);
+  return most;
+}
+
 static uint64_t total_particles(const std::vector<QueryDev>& hq) {
   uint64_t n = 0;
   for (const auto& q : hq) n += q.N;
@@ -466,7 +473,7 @@ static void layout(std::vector<QueryDev>& hq, uint64_t nt, uint64_t n_planes, bo
   const uint64_t stride = (words + 31) & ~31ull;  // whole cache lines
   const uint64_t o_tc = take(tl ? (stride << tl) * sizeof(long long) : 0);
   const uint64_t with_tally = off;
-  const bool rows = batch && total_particles(hq) >= std::max(nq * kLatOwnMinParticles, kLatOwnMinBatch);
+  const bool rows = batch && nq <= kMaxGridY && total_particles(hq) >= std::max(nq * kLatOwnMinParticles, kLatOwnMinBatch);
   const uint64_t o_lr = take(rows ? nq * kLatOwnStride * sizeof(float) : 0);
   L.bytes = off;
   L.lat_rows = rows && ws_bytes >= L.bytes ? reinterpret_cast<float*>(base + o_lr) : nullptr;
@@ -489,8 +496,7 @@ static void layout(std::vector<QueryDev>& hq, uint64_t nt, uint64_t n_planes, bo
   for (int k = 0; k < 6; ++k) L.planes[k] = reinterpret_cast<float*>(base + o_p[k]);
 }
 
-static TallyMode plain_mode(const QueryDev& q, uint64_t nt) {
-  if (!q.per_tri) return kTallyTotals;
+static TallyMode plain_mode(uint64_t nt) {  // of queries with per-triangle tallies
   if (nt <= (uint64_t)kLaneTallyMaxTris) return kTallyLane;
   if (nt <= (uint64_t)kLdsTallyMaxTris) return kTallyLds;
   return kTallyGlobal;
@@ -707,12 +713,6 @@ extern "C" tpmc_status tpmc_workspace_bytes(tpmc_ctx ctx, tpmc_mesh m, const tpm
   return TPMC_OK;
 }
 
-static int seed_grid(tpmc_ctx ctx, uint64_t n) {
-  const uint64_t g = (n + kBlock - 1) / kBlock;
-  const uint64_t cap = (uint64_t)ctx->n_cu * 16;
-  return (int)(g < cap ? (g ? g : 1) : cap);
-}
-
 extern "C" tpmc_status tpmc_seed(tpmc_ctx ctx, tpmc_mesh m, const tpmc_query* q, uint32_t nq, void* ws,
                                  uint64_t ws_bytes, tpmc_particles* out) {
   if (!ctx || !m || !out) return fail(TPMC_E_INVALID, "ctx, mesh and out must not be NULL");
@@ -751,13 +751,9 @@ extern "C" tpmc_status tpmc_seed(tpmc_ctx ctx, tpmc_mesh m, const tpmc_query* q,
   clear_ranges({{p->lay.scal, p->lay.tally, p->lay.copies.base, tc.base, nullptr},
                 {(uint64_t)nq * kScalarSlots, p->lay.tally_words, p->lay.copy_words, tc.stride << tc.log2, 0}},
                ctx->stream);
-  for (uint32_t i = 0; i < nq; ++i) {
-    const QueryDev& hq = p->hq[i];
-    float* const x[3] = {p->lay.planes[0] + hq.p_offset, p->lay.planes[1] + hq.p_offset,
-                         p->lay.planes[2] + hq.p_offset};
-    float* const w[3] = {p->lay.planes[3] + hq.p_offset, p->lay.planes[4] + hq.p_offset,
-                         p->lay.planes[5] + hq.p_offset};
-    launch_seed(p->lay.qs + i, hq.N, x, w, seed_grid(ctx, hq.N), ctx->stream);
+  for (uint32_t i = 0; i < nq; i += kMaxGridY) {
+    const uint32_t n = std::min(kMaxGridY, nq - i);
+    launch_seed(p->lay.qs + i, n, most_particles(p->hq, i, n), p->lay.planes, ctx->n_cu, ctx->stream);
   }
   e = hipGetLastError();
   if (e != hipSuccess) {
@@ -775,49 +771,40 @@ extern "C" tpmc_status tpmc_particles_planes(tpmc_particles p, float* dev_planes
   return TPMC_OK;
 }
 
-// Plain trace grid: at least four particles per lane (so that lanes whose
-// particle retires have another to take), at most plain_groups_per_cu per CU.
-// Every workgroup of a plain launch flushes its tallies and scalars with
-// device atomics once, onto the same few addresses for a small mesh, so the
-// cap is kept lower than the persistent launches' (whose workgroups flush once
-// per query they took part in).
-static int trace_grid(tpmc_ctx ctx, uint64_t n) {
-  const uint64_t g = (n + 4 * kBlock - 1) / (4 * kBlock);
-  const uint64_t cap = (uint64_t)ctx->n_cu * ctx->tune.plain_groups_per_cu;
-  return (int)(g < cap ? (g ? g : 1) : cap);
-}
-
 extern "C" tpmc_status tpmc_trace_ex(tpmc_ctx ctx, tpmc_mesh m, tpmc_particles p, int32_t* dev_first_tri,
                                      uint64_t* dev_counters, tpmc_tally* out) {
   if (!ctx || !m || !p || !out) return fail(TPMC_E_INVALID, "ctx, mesh, particles and out must not be NULL");
   *out = nullptr;
   if (p->mesh != m || p->ctx != ctx) return fail(TPMC_E_BUSY, "particles were seeded for another mesh or context");
   HIP_TRY(hipSetDevice(ctx->device));
-  for (uint32_t i = 0; i < p->nq; ++i) {
-    const QueryDev& hq = p->hq[i];
-    TraceArgs a;
-    a.nodes = m->nodes;
-    a.tris = m->tris;
-    a.orig = m->orig;
-    a.q = p->lay.qs + i;
-    for (int k = 0; k < 3; ++k) {
-      a.x[k] = p->lay.planes[k] + hq.p_offset;
-      a.w[k] = p->lay.planes[3 + k] + hq.p_offset;
-    }
-    a.n = hq.N;
-    a.tally = hq.per_tri ? p->lay.tally + hq.tally_offset : nullptr;
-    a.scal = p->lay.scal + hq.scalar_offset;
-    const ScalCopies& sc = p->lay.copies;
-    a.copies = sc.base ? sc.base + ((uint64_t)i << sc.log2) * kScalStride : nullptr;
-    a.copy_mask = (1u << sc.log2) - 1u;
-    a.tally_copies = p->lay.tally_copies;
-    if (!hq.per_tri) a.tally_copies.base = nullptr;
-    if (a.tally_copies.base) a.tally_copies.base += hq.tally_offset;
-    a.first_tri = dev_first_tri ? dev_first_tri + hq.p_offset : nullptr;
-    a.counters = reinterpret_cast<unsigned long long*>(dev_counters);
-    a.nt = (uint32_t)m->nt;
-    a.refill = ctx->tune.refill_lanes;
-    launch_trace(a, m->stack_slots, plain_mode(hq, m->nt), trace_grid(ctx, hq.N), ctx->stream);
+  bool kinds[2] = {false, false};  // some query keeps per-triangle tallies, some totals only
+  for (const auto& hq : p->hq) kinds[hq.per_tri ? 0 : 1] = true;
+  TraceArgs a;
+  a.nodes = m->nodes;
+  a.tris = m->tris;
+  a.orig = m->orig;
+  for (int k = 0; k < 3; ++k) {
+    a.x[k] = p->lay.planes[k];
+    a.w[k] = p->lay.planes[3 + k];
+  }
+  a.tally = p->lay.tally;
+  a.scal = p->lay.scal;
+  a.tally_copies = p->lay.tally_copies;
+  a.first_tri = dev_first_tri;
+  a.counters = reinterpret_cast<unsigned long long*>(dev_counters);
+  a.nt = (uint32_t)m->nt;
+  a.refill = ctx->tune.refill_lanes;
+  // at most plain_groups_per_cu workgroups per CU and query
+  const int max_grid = (int)(ctx->n_cu * ctx->tune.plain_groups_per_cu);
+  for (uint32_t i = 0; i < p->nq; i += kMaxGridY) {
+    const uint32_t n = std::min(kMaxGridY, p->nq - i);
+    a.qs = p->lay.qs + i;
+    a.copies = p->lay.copies;
+    if (a.copies.base) a.copies.base += ((uint64_t)i << a.copies.log2) * kScalStride;
+    for (int kind = 0; kind < 2; ++kind)
+      if (kinds[kind])
+        launch_trace(a, n, most_particles(p->hq, i, n), m->stack_slots,
+                     kind == 1 ? kTallyTotals : plain_mode(m->nt), max_grid, ctx->stream);
     HIP_CHECK_LAUNCH("trace");
   }
   if (p->lay.tally_copies.base) launch_fold_tally(p->lay.tally, p->lay.tally_copies, ctx->stream);
@@ -857,12 +844,6 @@ static void copy_result(const ResultDev& r, tpmc_result* o) {
   o->preculled = r.preculled;
 }
 
-// Clears the per-query totals the reduction writes (slots kFx..kCount).
-static void clear_totals(long long* scal, uint32_t nq, const std::vector<QueryDev>& hq, hipStream_t st) {
-  for (uint32_t i = 0; i < nq; ++i)
-    if (hq[i].per_tri) zero_i64(scal + hq[i].scalar_offset + kFx, 7, st);
-}
-
 static tpmc_status finalize_results(tpmc_ctx ctx, const Layout& L, uint32_t nq, const double ref_point[3],
                                     double A_ref, tpmc_result* out) {
   const double xr = ref_point ? ref_point[0] : 0.0, yr = ref_point ? ref_point[1] : 0.0,
@@ -884,11 +865,11 @@ extern "C" tpmc_status tpmc_forces(tpmc_ctx ctx, tpmc_tally t, const double ref_
   tpmc_particles p = t->p;
   if (p->ctx != ctx) return fail(TPMC_E_BUSY, "tally belongs to another context");
   HIP_TRY(hipSetDevice(ctx->device));
-  clear_totals(p->lay.scal, p->nq, p->hq, ctx->stream);
-  for (uint32_t i = 0; i < p->nq; ++i)
-    if (p->hq[i].per_tri)
-      launch_reduce(p->lay.tally + p->hq[i].tally_offset, (uint32_t)p->mesh->nt,
-                    p->lay.scal + p->hq[i].scalar_offset, ctx->stream);
+  bool any_tri = false;
+  for (const auto& hq : p->hq) any_tri = any_tri || hq.per_tri;
+  for (uint32_t i = 0; any_tri && i < p->nq; i += kMaxGridY)
+    launch_reduce_totals(p->lay.qs + i, std::min(kMaxGridY, p->nq - i), p->lay.tally, p->lay.scal,
+                         (uint32_t)p->mesh->nt, ctx->stream);
   HIP_CHECK_LAUNCH("reduce");
   return finalize_results(ctx, p->lay, p->nq, ref_point, A_ref, out);
 }

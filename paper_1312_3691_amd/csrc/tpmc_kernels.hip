@@ -159,12 +159,20 @@ __global__ __launch_bounds__(kBlock) void lat_own_kernel(const QueryDev* __restr
   if (q.lat_own && j < kLatFNT) rows[(uint64_t)blockIdx.y * kLatOwnStride + j] = latitude_row(q, g_lat_fine, j);
 }
 
-__global__ __launch_bounds__(kBlock) void seed_kernel(const QueryDev* __restrict__ qp, uint64_t n,
-                                                      float* __restrict__ x0, float* __restrict__ x1,
-                                                      float* __restrict__ x2, float* __restrict__ w0,
-                                                      float* __restrict__ w1, float* __restrict__ w2) {
-  const QueryDev& q = *qp;
-  const uint64_t stride = (uint64_t)gridDim.x * kBlock;
+struct Planes {
+  float* p[6];
+};
+
+// Query blockIdx.y.
+__global__ __launch_bounds__(kBlock) void seed_kernel(const QueryDev* __restrict__ qs, Planes planes) {
+  const QueryDev& q = qs[blockIdx.y];
+  float* __restrict__ const x0 = planes.p[0] + q.p_offset;
+  float* __restrict__ const x1 = planes.p[1] + q.p_offset;
+  float* __restrict__ const x2 = planes.p[2] + q.p_offset;
+  float* __restrict__ const w0 = planes.p[3] + q.p_offset;
+  float* __restrict__ const w1 = planes.p[4] + q.p_offset;
+  float* __restrict__ const w2 = planes.p[5] + q.p_offset;
+  const uint64_t n = q.N, stride = (uint64_t)gridDim.x * kBlock;
   for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += stride) {
     double x[3], w[3];
     seed_particle(q, g_lat_start, g_lat_fine, nullptr, g_vn_start, g_sc_tab, g_ee_tab, i, x, w);
@@ -665,22 +673,38 @@ __device__ __forceinline__ void flush_acc(Acc& A, long long* __restrict__ scal, 
 }
 
 // ---------------------------------------------------------------------------
-// a6-a9, plain path: one query per launch, particles read from the SoA.  Each
-// loop iteration advances every traversing lane by one BVH step.  Lanes whose
-// segment has ended wait until fewer than a.refill lanes are still
-// traversing; then all of them are served at once (re-emission, tallies, the
-// next segment, or the next particle by grid stride), so the costly per-hit
-// work runs with many lanes active and no lane idles for the rest of a
-// segment's traversal.
+// a6-a9, plain path: particles read from the SoA.  Each loop iteration advances
+// every traversing lane by one BVH step.  Lanes whose segment has ended wait
+// until fewer than a.refill lanes are still traversing; then all of them are
+// served at once (re-emission, tallies, the next segment, or the wave's next
+// particle), so the costly per-hit work runs with many lanes active and no lane
+// idles for the rest of a segment's traversal.  A wave has a share of
+// consecutive particles, and the lanes that need one take the next ones in
+// order, so that a load of the SoA covers whole cache lines and each line is
+// fetched once.  With a particle per lane and grid stride every lane was at
+// another stride, a line for each: 1e6 particles on a plate 416 us, 52 now; 3e6
+// on a cylinder 649, 296 now.
 // ---------------------------------------------------------------------------
+// Workgroups of a query of n particles in a launch of max_groups a query: a
+// particle per lane while they suffice (four per lane at least took 162 us for
+// 1e5 particles on the 1280-triangle sphere, on 98 of 256 compute units, LATER now).
+__host__ __device__ __forceinline__ uint64_t plain_groups(uint64_t n, uint32_t max_groups) {
+  const uint64_t g = (n + kBlock - 1) / kBlock;
+  return g < max_groups ? g : max_groups;
+}
+
 template <int STACK, int MODE, bool COUNT>
 __global__ __launch_bounds__(kBlock) void trace_kernel(TraceArgs a) {
   __shared__ int stk[STACK][kBlock];
   extern __shared__ unsigned long long lt[];  // tallies in LDS, sized at launch (tally_lds_bytes)
-  const QueryDev& q = *a.q;
-  long long* const g_tally = a.tally_copies.base
-                                 ? a.tally_copies.base + (blockIdx.x & ((1u << a.tally_copies.log2) - 1u)) * a.tally_copies.stride
-                                 : a.tally;
+  const QueryDev& q = a.qs[blockIdx.y];
+  const uint64_t groups = plain_groups(q.N, gridDim.x);
+  if (blockIdx.x >= groups || (q.per_tri != 0u) != (MODE != kTallyTotals)) return;
+  const uint32_t group = blockIdx.y * gridDim.x + blockIdx.x;  // group % 8: the XCD
+  long long* const g_tally =
+      (a.tally_copies.base ? a.tally_copies.base + (group & ((1u << a.tally_copies.log2) - 1u)) * a.tally_copies.stride
+                           : a.tally) + q.tally_offset;
+  int32_t* const first_tri = a.first_tri ? a.first_tri + q.p_offset : nullptr;
   if (MODE == kTallyLds) {
     for (uint32_t i = threadIdx.x; i < a.nt * 7u; i += kBlock) lt[i] = 0ull;
     __syncthreads();
@@ -689,22 +713,30 @@ __global__ __launch_bounds__(kBlock) void trace_kernel(TraceArgs a) {
     for (int c = 0; c < 2 * 7; ++c) lt[c * kBlock + threadIdx.x] = 0ull;
   Acc A;
   acc_zero(A);
-  const uint64_t stride = (uint64_t)gridDim.x * kBlock;
   const uint32_t max_steps = 2u * a.nt + 64u;
+  uint64_t next, end;  // the wave's particles not yet taken (uniform)
+  {
+    const uint64_t waves = groups * kWaves, share = q.N / waves, rest = q.N % waves;
+    const uint32_t w = __builtin_amdgcn_readfirstlane(blockIdx.x * kWaves + (threadIdx.x >> 6));
+    next = share * w + (w < rest ? w : rest);
+    end = next + share + (w < rest ? 1u : 0u);
+  }
   Lane L;
   Seg s;
   Ray r;
   seg_begin(s);
   auto load = [&](Lane& l) {
-    l.ox = a.x[0][l.pid]; l.oy = a.x[1][l.pid]; l.oz = a.x[2][l.pid];
-    l.wx = a.w[0][l.pid]; l.wy = a.w[1][l.pid]; l.wz = a.w[2][l.pid];
+    const uint64_t i = q.p_offset + l.pid;
+    l.ox = a.x[0][i]; l.oy = a.x[1][i]; l.oz = a.x[2][i];
+    l.wx = a.w[0][i]; l.wy = a.w[1][i]; l.wz = a.w[2][i];
     l.D = 0.0f;
     l.E = 0.0f;
     l.prev = -1;
     l.hits = 0;
   };
-  L.pid = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
-  L.live = L.pid < a.n;
+  L.pid = next + (threadIdx.x & 63u);
+  L.live = L.pid < end;
+  next += 64;
   s.cur = kDone;
   if (L.live) {
     load(L);
@@ -729,16 +761,17 @@ __global__ __launch_bounds__(kBlock) void trace_kernel(TraceArgs a) {
         if (fin) out = finish_segment(a.tris, a.orig, q, L, s, h, fid, limited);
         count_pass(A, fin, out, h.valid, limited);
         tally<MODE, STACK, false>(q, h, g_tally, lt, stk, A);
-        if (fin) {
-          if (a.first_tri && fid != -2) a.first_tri[L.pid] = fid;
-          if (out != kOutGoOn) {
-            retire(q, L, A);
-            L.pid += stride;
-            L.live = L.pid < a.n;
-            if (L.live) load(L);
-          }
-          if (L.live) seg_begin(s);
+        if (fin && first_tri && fid != -2) first_tri[L.pid] = fid;
+        const bool take = fin && out != kOutGoOn;
+        const uint64_t taken = ballot(take);
+        if (take) {
+          retire(q, L, A);
+          L.pid = next + below(taken);
+          L.live = L.pid < end;
+          if (L.live) load(L);
         }
+        next += (uint32_t)__popcll(taken);
+        if (fin && L.live) seg_begin(s);
       }
       make_ray(r, L.ox, L.oy, L.oz, L.wx, L.wy, L.wz);
       guard = 0;
@@ -753,7 +786,9 @@ __global__ __launch_bounds__(kBlock) void trace_kernel(TraceArgs a) {
     if (L.live && seg_traversing(s))
       trav_step<STACK, COUNT>(a.nodes, a.tris, a.orig, r, L.prev, s, stk, A.nodes, A.tests);
   }
-  flush_acc(A, a.copies ? a.copies + (uint64_t)(blockIdx.x & a.copy_mask) * kScalStride : a.scal, MODE == kTallyTotals);
+  flush_acc(A, a.copies.base ? a.copies.base + (((uint64_t)blockIdx.y << a.copies.log2) +
+                                                (group & ((1u << a.copies.log2) - 1u))) * kScalStride
+                             : a.scal + q.scalar_offset, MODE == kTallyTotals);
   if (MODE == kTallyLane) flush_lane_tally(lt, g_tally, a.nt);
   if (COUNT) {
     const long long nn = wave_sum((long long)A.nodes), nt2 = wave_sum((long long)A.tests);
@@ -1328,11 +1363,6 @@ __device__ __forceinline__ void reduce_one(const long long* __restrict__ tally, 
   }
 }
 
-__global__ __launch_bounds__(kBlock) void reduce_kernel(const long long* __restrict__ tally, uint32_t nt,
-                                                        long long* __restrict__ scal) {
-  reduce_one(tally, 1u, 0u, nt, scal, blockIdx.x);
-}
-
 __global__ __launch_bounds__(kBlock) void reduce_batch_kernel(const QueryDev* __restrict__ qs,
                                                               long long* __restrict__ tally_base, TallyCopies copies,
                                                               long long* __restrict__ scal_base) {
@@ -1443,7 +1473,7 @@ size_t tally_lds_bytes(TallyMode mode, uint32_t lds_tris, bool persistent, bool 
 }
 
 template <int STACK, bool COUNT>
-void launch_trace_mode(const TraceArgs& a, TallyMode mode, int grid, hipStream_t st) {
+void launch_trace_mode(const TraceArgs& a, TallyMode mode, dim3 grid, hipStream_t st) {
   const size_t lds = tally_lds_bytes(mode, a.nt, false);
   switch (mode) {
     case kTallyGlobal: trace_kernel<STACK, kTallyGlobal, COUNT><<<grid, kBlock, lds, st>>>(a); break;
@@ -1454,7 +1484,7 @@ void launch_trace_mode(const TraceArgs& a, TallyMode mode, int grid, hipStream_t
 }
 
 template <int STACK>
-void launch_trace_stack(const TraceArgs& a, TallyMode mode, int grid, hipStream_t st) {
+void launch_trace_stack(const TraceArgs& a, TallyMode mode, dim3 grid, hipStream_t st) {
   if (a.counters) launch_trace_mode<STACK, true>(a, mode, grid, st);
   else launch_trace_mode<STACK, false>(a, mode, grid, st);
 }
@@ -1610,11 +1640,16 @@ int stack_slots_for_depth(uint32_t depth) {
   return 0;
 }
 
-void launch_seed(const QueryDev* d_q, uint64_t n, float* const x[3], float* const w[3], int grid, hipStream_t st) {
-  seed_kernel<<<grid, kBlock, 0, st>>>(d_q, n, x[0], x[1], x[2], w[0], w[1], w[2]);
+void launch_seed(const QueryDev* d_qs, uint32_t nq, uint64_t max_n, float* const planes[6], int n_cu, hipStream_t st) {
+  const uint64_t g = std::min<uint64_t>((max_n + kBlock - 1) / kBlock, (uint64_t)n_cu * 16);
+  Planes p;
+  for (int k = 0; k < 6; ++k) p.p[k] = planes[k];
+  seed_kernel<<<dim3((uint32_t)std::max<uint64_t>(g, 1), nq), kBlock, 0, st>>>(d_qs, p);
 }
 
-void launch_trace(const TraceArgs& a, int stack_slots, TallyMode mode, int grid, hipStream_t st) {
+void launch_trace(const TraceArgs& a, uint32_t nq, uint64_t max_n, int stack_slots, TallyMode mode, int max_grid,
+                  hipStream_t st) {
+  const dim3 grid((uint32_t)std::max<uint64_t>(plain_groups(max_n, (uint32_t)max_grid), 1), nq);
   switch (stack_slots) {
     case 4: launch_trace_stack<4>(a, mode, grid, st); break;
     case 8: launch_trace_stack<8>(a, mode, grid, st); break;
@@ -1656,11 +1691,6 @@ void launch_batch(BatchArgs a, int stack_slots, TallyMode mode, uint64_t total_p
   }
 }
 
-void launch_reduce(const long long* tally, uint32_t nt, long long* scal, hipStream_t st) {
-  const int g = (int)((nt + kReduceChunk - 1) / kReduceChunk);
-  reduce_kernel<<<g, kBlock, 0, st>>>(tally, nt, scal);
-}
-
 void launch_reduce_batch(const QueryDev* d_qs, uint32_t nq, long long* tally_base, const TallyCopies& copies,
                          long long* scal_base, uint32_t max_nt, hipStream_t st) {
   dim3 g((max_nt + kReduceChunk - 1) / kReduceChunk, nq);
@@ -1700,6 +1730,12 @@ void launch_reduce_slots(const QueryDev* d_qs, const uint32_t* d_idx, uint32_t n
   clear_totals_kernel<<<(n * 7 + 255) / 256, 256, 0, st>>>(d_qs, d_idx, scal_base, n);
   dim3 g((max_nt + kReduceChunk - 1) / kReduceChunk, n);
   reduce_slots_kernel<<<g, kBlock, 0, st>>>(d_qs, d_idx, tally_base, scal_base);
+}
+
+void launch_reduce_totals(const QueryDev* d_qs, uint32_t nq, long long* tally_base, long long* scal_base,
+                          uint32_t max_nt, hipStream_t st) {
+  clear_totals_kernel<<<(nq * 7 + 255) / 256, 256, 0, st>>>(d_qs, nullptr, scal_base, nq);
+  launch_reduce_batch(d_qs, nq, tally_base, TallyCopies{nullptr, 0, 0}, scal_base, max_nt, st);
 }
 
 }  // namespace tpmc

@@ -34,20 +34,20 @@ struct TallyCopies {
   uint64_t stride;
 };
 
+// A launch covers the queries qs[0, gridDim.y) of one tally kind (the others'
+// workgroups leave at once), workgroups x of query y.
 struct TraceArgs {
   const Node* nodes;
   const TriRec* tris;
   const uint32_t* orig;
-  const QueryDev* q;          // device pointer, one query
-  const float* x[3];          // SoA planes, already offset to the query
+  const QueryDev* qs;         // device pointer
+  const float* x[3];          // SoA planes
   const float* w[3];
-  uint64_t n;
-  long long* tally;           // [nt][7] or null (totals mode)
-  long long* scal;            // [kScalarSlots]
-  long long* copies;          // the query's ScalCopies (null: none), 1 + copy_mask of them
-  uint32_t copy_mask;
-  TallyCopies tally_copies;   // base null or offset to the query
-  int32_t* first_tri;         // optional, already offset to the query
+  long long* tally;           // indexed by QueryDev::tally_offset
+  long long* scal;            // indexed by QueryDev::scalar_offset
+  ScalCopies copies;          // of the blocks of qs
+  TallyCopies tally_copies;   // of the words at tally
+  int32_t* first_tri;         // optional, indexed by QueryDev::p_offset
   unsigned long long* counters;  // optional [2]: BVH nodes visited, triangle tests
   uint32_t nt;
   uint32_t refill;            // serve ended segments when fewer lanes of a wave traverse (1..64)
@@ -123,9 +123,14 @@ hipError_t build_bvh_sah(const float* d_xyz, const uint32_t* d_tri, uint64_t nt,
                          TriRec* d_tris, uint32_t* d_orig, uint32_t* h_depth, hipStream_t st);
 
 int stack_slots_for_depth(uint32_t depth);  // 0 when too deep
-void launch_seed(const QueryDev* d_q, uint64_t n, float* const x[3], float* const w[3], int grid, hipStream_t st);
-void launch_trace(const TraceArgs& a, int stack_slots, TallyMode mode, int grid, hipStream_t st);
-void launch_reduce(const long long* tally, uint32_t nt, long long* scal, hipStream_t st);
+// Plain path: one launch of up to kMaxGridY queries each, max_n particles in the largest.
+constexpr uint32_t kMaxGridY = 65535;
+void launch_seed(const QueryDev* d_qs, uint32_t nq, uint64_t max_n, float* const planes[6], int n_cu, hipStream_t st);
+void launch_trace(const TraceArgs& a, uint32_t nq, uint64_t max_n, int stack_slots, TallyMode mode, int max_grid,
+                  hipStream_t st);
+// Clears the queries' totals, then sums their triangles (plain path).
+void launch_reduce_totals(const QueryDev* d_qs, uint32_t nq, long long* tally_base, long long* scal_base,
+                          uint32_t max_nt, hipStream_t st);
 void launch_finalize(const QueryDev* d_qs, const uint32_t* d_idx, const long long* scal_base, const ScalCopies& copies,
                      uint32_t nq, double xr, double yr, double zr, double A_ref, ResultDev* out, hipStream_t st);
 void launch_reduce_slots(const QueryDev* d_qs, const uint32_t* d_idx, uint32_t n, long long* tally_base,

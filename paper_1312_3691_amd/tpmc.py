@@ -388,7 +388,7 @@ class Mesh:
 
 class PlainRun:
     """seed -> trace -> forces for a list of queries (one kernel launch per
-    query and stage).  Keeps the workspace alive while its handles live."""
+    stage; two for a trace of both tally kinds).  Keeps the workspace alive while its handles live."""
 
     def __init__(self, mesh: Mesh, queries, first_tri: bool = False):
         torch = _torch()
