@@ -67,7 +67,42 @@ struct tpmc_ctx_s {
   hipStream_t capture_stream;
   int n_cu;
   tpmc_tuning tune;
+  // Pinned host memory of kHostResults results that finalize writes small calls'
+  // results to (null: none), held by one call at a time; another takes the copy
+  // from device memory.
+  ResultDev* host_res;
+  std::mutex host_res_mu;
 };
+
+// The pinned blocks of the process's contexts: one allocation (90 us, and a
+// wait for the device when freed) made with the first context, a block held
+// from a context's creation to its destruction; contexts beyond them have none.
+constexpr uint32_t kHostResults = 64, kHostBlocks = 32;
+static std::mutex g_blocks_mu;
+static ResultDev* g_blocks = nullptr;
+static uint32_t g_blocks_used = 0;  // bit b: block b is held
+
+static ResultDev* take_host_block() {
+  std::lock_guard<std::mutex> lock(g_blocks_mu);
+  if (!g_blocks && hipHostMalloc(reinterpret_cast<void**>(&g_blocks), kHostBlocks * kHostResults * sizeof(ResultDev),
+                                 hipHostMallocPortable) != hipSuccess) {
+    (void)hipGetLastError();
+    g_blocks = nullptr;
+    return nullptr;
+  }
+  for (uint32_t b = 0; b < kHostBlocks; ++b)
+    if (!(g_blocks_used >> b & 1u)) {
+      g_blocks_used |= 1u << b;
+      return g_blocks + (size_t)b * kHostResults;
+    }
+  return nullptr;
+}
+
+static void give_host_block(ResultDev* p) {
+  if (!p) return;
+  std::lock_guard<std::mutex> lock(g_blocks_mu);
+  g_blocks_used &= ~(1u << (uint32_t)((p - g_blocks) / kHostResults));
+}
 
 struct tpmc_mesh_s {
   tpmc_ctx ctx;
@@ -547,6 +582,7 @@ extern "C" tpmc_status tpmc_create(int device, void* hip_stream, tpmc_ctx* out) 
   c->tune.tile_particles = 16384;
   c->tune.groups_per_cu = 8;
   c->tune.plain_groups_per_cu = kPlainGroupsPerCu;
+  c->host_res = take_host_block();
   *out = c;
   return TPMC_OK;
 }
@@ -580,6 +616,7 @@ extern "C" tpmc_status tpmc_set_stream(tpmc_ctx ctx, void* hip_stream) {
 
 extern "C" void tpmc_destroy_ctx(tpmc_ctx ctx) {
   if (!ctx) return;
+  give_host_block(ctx->host_res);
   if (ctx->capture_stream) {
     (void)hipSetDevice(ctx->device);
     (void)hipStreamDestroy(ctx->capture_stream);
@@ -740,17 +777,20 @@ extern "C" tpmc_status tpmc_seed(tpmc_ctx ctx, tpmc_mesh m, const tpmc_query* q,
     delete p;
     return s;
   }
+  const TallyCopies& tc = p->lay.tally_copies;
+  const ClearRanges clear{{p->lay.scal, p->lay.tally, p->lay.copies.base, tc.base, nullptr},
+                          {(uint64_t)nq * kScalarSlots, p->lay.tally_words, p->lay.copy_words, tc.stride << tc.log2, 0}};
   hipError_t e = hipSetDevice(ctx->device);
-  if (e == hipSuccess)
+  if (e == hipSuccess && nq <= kArgQueries) {
+    clear_and_upload(clear, p->hq.data(), p->lay.qs, nq, ctx->stream);
+  } else if (e == hipSuccess) {
     e = hipMemcpyAsync(p->lay.qs, p->hq.data(), nq * sizeof(QueryDev), hipMemcpyHostToDevice, ctx->stream);
+    clear_ranges(clear, ctx->stream);
+  }
   if (e != hipSuccess) {
     delete p;
     return fail(TPMC_E_DEVICE, "query upload: %s", hipGetErrorString(e));
   }
-  const TallyCopies& tc = p->lay.tally_copies;
-  clear_ranges({{p->lay.scal, p->lay.tally, p->lay.copies.base, tc.base, nullptr},
-                {(uint64_t)nq * kScalarSlots, p->lay.tally_words, p->lay.copy_words, tc.stride << tc.log2, 0}},
-               ctx->stream);
   for (uint32_t i = 0; i < nq; i += kMaxGridY) {
     const uint32_t n = std::min(kMaxGridY, nq - i);
     launch_seed(p->lay.qs + i, n, most_particles(p->hq, i, n), p->lay.planes, ctx->n_cu, ctx->stream);
@@ -844,11 +884,22 @@ static void copy_result(const ResultDev& r, tpmc_result* o) {
   o->preculled = r.preculled;
 }
 
-static tpmc_status finalize_results(tpmc_ctx ctx, const Layout& L, uint32_t nq, const double ref_point[3],
-                                    double A_ref, tpmc_result* out) {
+// tally_copies: those that still hold the per-triangle sums (a plain run has folded them).
+static tpmc_status finalize_results(tpmc_ctx ctx, const Layout& L, const TallyCopies& tally_copies, uint64_t nt,
+                                    uint32_t nq, const double ref_point[3], double A_ref, tpmc_result* out) {
   const double xr = ref_point ? ref_point[0] : 0.0, yr = ref_point ? ref_point[1] : 0.0,
                zr = ref_point ? ref_point[2] : 0.0;
-  launch_finalize(L.qs, nullptr, L.scal, L.copies, nq, xr, yr, zr, A_ref, L.res, ctx->stream);
+  const long long* const tally = nt <= kFinalizeTris ? L.tally : nullptr;
+  std::unique_lock<std::mutex> pinned(ctx->host_res_mu, std::defer_lock);
+  if (nq <= kHostResults && ctx->host_res && pinned.try_lock()) {
+    launch_finalize(L.qs, nullptr, L.scal, L.copies, tally, tally_copies, nq, xr, yr, zr, A_ref, ctx->host_res,
+                    ctx->stream);
+    HIP_CHECK_LAUNCH("finalize");
+    HIP_TRY(hipStreamSynchronize(ctx->stream));
+    for (uint32_t i = 0; i < nq; ++i) copy_result(ctx->host_res[i], out + i);
+    return TPMC_OK;
+  }
+  launch_finalize(L.qs, nullptr, L.scal, L.copies, tally, tally_copies, nq, xr, yr, zr, A_ref, L.res, ctx->stream);
   HIP_CHECK_LAUNCH("finalize");
   std::vector<ResultDev> hr(nq);
   HIP_TRY(hipMemcpyAsync(hr.data(), L.res, nq * sizeof(ResultDev), hipMemcpyDeviceToHost, ctx->stream));
@@ -867,11 +918,11 @@ extern "C" tpmc_status tpmc_forces(tpmc_ctx ctx, tpmc_tally t, const double ref_
   HIP_TRY(hipSetDevice(ctx->device));
   bool any_tri = false;
   for (const auto& hq : p->hq) any_tri = any_tri || hq.per_tri;
-  for (uint32_t i = 0; any_tri && i < p->nq; i += kMaxGridY)
+  for (uint32_t i = 0; any_tri && p->mesh->nt > kFinalizeTris && i < p->nq; i += kMaxGridY)
     launch_reduce_totals(p->lay.qs + i, std::min(kMaxGridY, p->nq - i), p->lay.tally, p->lay.scal,
                          (uint32_t)p->mesh->nt, ctx->stream);
   HIP_CHECK_LAUNCH("reduce");
-  return finalize_results(ctx, p->lay, p->nq, ref_point, A_ref, out);
+  return finalize_results(ctx, p->lay, TallyCopies{nullptr, 0, 0}, p->hq[0].nt, p->nq, ref_point, A_ref, out);
 }
 
 extern "C" tpmc_status tpmc_tally_copy(tpmc_ctx ctx, tpmc_tally t, uint32_t query, double* host_per_tri) {
@@ -931,10 +982,11 @@ extern "C" tpmc_status tpmc_batch_workspace_bytes(tpmc_ctx ctx, tpmc_mesh m, con
   return TPMC_OK;
 }
 
-// Fills b for the queries q on mesh m with its workspace at ws (ws_bytes) and
-// uploads the query table (synchronises).  Allocates nothing.
+// Fills b for the queries q on mesh m with its workspace at ws (ws_bytes) and,
+// if upload, uploads the query table and makes the own latitude rows
+// (synchronises).  Allocates nothing.
 static tpmc_status batch_init(tpmc_ctx ctx, tpmc_mesh m, const tpmc_query* q, uint32_t nq, void* ws,
-                              uint64_t ws_bytes, tpmc_batch_s* b) {
+                              uint64_t ws_bytes, bool upload, tpmc_batch_s* b) {
   tpmc_status s = batch_prepare(m, q, nq, b->hq, b->lay, static_cast<uint8_t*>(ws), ws_bytes);
   if (s == TPMC_OK) s = check_ws(ws, ws_bytes, b->lay.need);
   if (s != TPMC_OK) return s;
@@ -960,6 +1012,7 @@ static tpmc_status batch_init(tpmc_ctx ctx, tpmc_mesh m, const tpmc_query* q, ui
   b->exec = nullptr;
   b->launched = false;
   hipError_t e = hipSetDevice(ctx->device);
+  if (e == hipSuccess && !upload) return TPMC_OK;
   if (e == hipSuccess)
     e = hipMemcpyAsync(b->lay.qs, b->hq.data(), nq * sizeof(QueryDev), hipMemcpyHostToDevice, ctx->stream);
   if (e == hipSuccess && b->lay.lat_rows) {
@@ -978,7 +1031,7 @@ extern "C" tpmc_status tpmc_batch_create(tpmc_ctx ctx, tpmc_mesh m, const tpmc_q
   if (m->ctx != ctx) return fail(TPMC_E_BUSY, "mesh belongs to another context");
   tpmc_batch b = new (std::nothrow) tpmc_batch_s;
   if (!b) return fail(TPMC_E_INVALID, "out of host memory");
-  const tpmc_status s = batch_init(ctx, m, q, nq, ws, ws_bytes, b);
+  const tpmc_status s = batch_init(ctx, m, q, nq, ws, ws_bytes, true, b);
   if (s != TPMC_OK) {
     delete b;
     return s;
@@ -987,12 +1040,20 @@ extern "C" tpmc_status tpmc_batch_create(tpmc_ctx ctx, tpmc_mesh m, const tpmc_q
   return TPMC_OK;
 }
 
-static void batch_enqueue(tpmc_batch b, hipStream_t st) {
+// upload: the query table is still to be written (nq <= kArgQueries).
+static void batch_enqueue(tpmc_batch b, bool upload, hipStream_t st) {
   tpmc_mesh m = b->mesh;
   const TallyCopies& tc = b->lay.tally_copies;
-  clear_ranges({{reinterpret_cast<long long*>(b->lay.next), b->lay.scal, b->lay.tally, b->lay.copies.base, tc.base},
-                {b->lay.counters, (uint64_t)b->nq * kScalarSlots, tc.base ? 0 : b->lay.tally_words,
-                 b->lay.copy_words, tc.stride << tc.log2}}, st);
+  const ClearRanges clear{
+      {reinterpret_cast<long long*>(b->lay.next), b->lay.scal, b->lay.tally, b->lay.copies.base, tc.base},
+      {b->lay.counters, (uint64_t)b->nq * kScalarSlots, tc.base ? 0 : b->lay.tally_words, b->lay.copy_words,
+       tc.stride << tc.log2}};
+  if (upload) {
+    clear_and_upload(clear, b->hq.data(), b->lay.qs, b->nq, st);
+    if (b->lay.lat_rows) launch_lat_own(b->lay.qs, b->nq, b->lay.lat_rows, st);
+  } else {
+    clear_ranges(clear, st);
+  }
   BatchArgs a{};
   a.qs = b->lay.qs;
   a.entry_query = nullptr;
@@ -1009,7 +1070,8 @@ static void batch_enqueue(tpmc_batch b, hipStream_t st) {
   a.lds_tris = b->mode == kTallyLds ? (uint32_t)m->nt : 0u;
   a.wave_totals = b->mode == kTallyTotals ? 1u : 0u;
   launch_batch(a, m->stack_slots, b->mode, b->total_particles, true, b->lay.counters, b->n_cu, b->groups_per_cu, st);
-  if (b->mode != kTallyTotals) launch_reduce_batch(b->lay.qs, b->nq, b->lay.tally, tc, b->lay.scal, (uint32_t)m->nt, st);
+  if (b->mode != kTallyTotals && m->nt > kFinalizeTris)
+    launch_reduce_batch(b->lay.qs, b->nq, b->lay.tally, tc, b->lay.scal, (uint32_t)m->nt, st);
 }
 
 extern "C" tpmc_status tpmc_batch_launch(tpmc_ctx ctx, tpmc_batch b, int use_graph) {
@@ -1017,7 +1079,7 @@ extern "C" tpmc_status tpmc_batch_launch(tpmc_ctx ctx, tpmc_batch b, int use_gra
   if (b->ctx != ctx) return fail(TPMC_E_BUSY, "batch belongs to another context");
   HIP_TRY(hipSetDevice(ctx->device));
   if (!use_graph) {
-    batch_enqueue(b, ctx->stream);
+    batch_enqueue(b, false, ctx->stream);
     HIP_CHECK_LAUNCH("batch");
     b->launched = true;
     return TPMC_OK;
@@ -1026,7 +1088,7 @@ extern "C" tpmc_status tpmc_batch_launch(tpmc_ctx ctx, tpmc_batch b, int use_gra
     if (!ctx->capture_stream) HIP_TRY(hipStreamCreateWithFlags(&ctx->capture_stream, hipStreamNonBlocking));
     hipGraph_t graph = nullptr;
     HIP_TRY(hipStreamBeginCapture(ctx->capture_stream, hipStreamCaptureModeThreadLocal));
-    batch_enqueue(b, ctx->capture_stream);
+    batch_enqueue(b, false, ctx->capture_stream);
     hipError_t e = hipStreamEndCapture(ctx->capture_stream, &graph);
     if (e != hipSuccess) return fail(TPMC_E_DEVICE, "graph capture: %s", hipGetErrorString(e));
     e = hipGraphInstantiate(&b->exec, graph, nullptr, nullptr, 0);
@@ -1048,7 +1110,7 @@ extern "C" tpmc_status tpmc_batch_results(tpmc_ctx ctx, tpmc_batch b, const doub
   if (ref_point && !finite3(ref_point)) return fail(TPMC_E_INVALID, "reference point must be finite");
   if (!b->launched) return fail(TPMC_E_BUSY, "batch has not been launched");
   HIP_TRY(hipSetDevice(ctx->device));
-  return finalize_results(ctx, b->lay, b->nq, ref_point, A_ref, out);
+  return finalize_results(ctx, b->lay, b->lay.tally_copies, b->hq[0].nt, b->nq, ref_point, A_ref, out);
 }
 
 extern "C" void tpmc_destroy_batch(tpmc_batch b) {
@@ -1084,11 +1146,12 @@ extern "C" tpmc_status tpmc_batch_run_noalloc(tpmc_ctx ctx, tpmc_mesh m, const t
   if (L.need > kScratchBytes)
     return fail(TPMC_E_WORKSPACE, "these queries need %llu bytes of workspace; the static workspace holds %llu",
                 (unsigned long long)L.need, (unsigned long long)kScratchBytes);
-  s = batch_init(ctx, m, q, nq, ws, kScratchBytes, &b);
+  const bool by_args = nq <= kArgQueries;
+  s = batch_init(ctx, m, q, nq, ws, kScratchBytes, !by_args, &b);
   if (s != TPMC_OK) return s;
-  batch_enqueue(&b, ctx->stream);  // zeroes the claim counters, scalars and tallies it uses
+  batch_enqueue(&b, by_args, ctx->stream);  // zeroes the claim counters, scalars and tallies it uses
   HIP_CHECK_LAUNCH("batch");
-  return finalize_results(ctx, b.lay, nq, ref_point, A_ref, out);
+  return finalize_results(ctx, b.lay, b.lay.tally_copies, m->nt, nq, ref_point, A_ref, out);
 }
 
 // ---------------------------------------------------------------------------
@@ -1393,7 +1456,7 @@ extern "C" tpmc_status tpmc_server_collect(tpmc_server s, const uint32_t* slots,
   launch_reduce_slots(s->qs, idx, n, s->tally, s->scal, max_nt, st);
   const double xr = ref_point ? ref_point[0] : 0.0, yr = ref_point ? ref_point[1] : 0.0,
                zr = ref_point ? ref_point[2] : 0.0;
-  launch_finalize(s->qs, idx, s->scal, s->copies, n, xr, yr, zr, A_ref, res, st);
+  launch_finalize(s->qs, idx, s->scal, s->copies, nullptr, TallyCopies{nullptr, 0, 0}, n, xr, yr, zr, A_ref, res, st);
   HIP_CHECK_LAUNCH("server collect");
   HIP_TRY(hipMemcpyAsync(s->res_host + (uint64_t)b * s->max_slots, res, n * sizeof(ResultDev), hipMemcpyDeviceToHost,
                          st));

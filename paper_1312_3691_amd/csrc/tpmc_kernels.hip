@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstring>
 #include <utility>
 
 #include "tpmc_device.hpp"
@@ -34,6 +35,23 @@ __global__ void zero_i64_kernel(long long* __restrict__ p, uint64_t n) {
 
 // Several ranges in one launch (the work of a launch costs less than the launch).
 __global__ void clear_kernel(ClearRanges r) {
+  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+#pragma unroll
+  for (int k = 0; k < kClearRanges; ++k)
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < r.n[k]; i += stride) r.p[k][i] = 0;
+}
+
+struct ArgQueries {
+  QueryDev q[kArgQueries];
+};
+static_assert(sizeof(ArgQueries) + sizeof(ClearRanges) + 64 <= 4096, "kernel arguments");
+
+__global__ void clear_upload_kernel(ClearRanges r, ArgQueries h, QueryDev* __restrict__ qs, uint32_t n) {
+  if (blockIdx.x == 0) {
+    const uint64_t* src = reinterpret_cast<const uint64_t*>(&h);
+    uint64_t* dst = reinterpret_cast<uint64_t*>(qs);
+    for (uint32_t w = threadIdx.x; w < n * (uint32_t)(sizeof(QueryDev) / 8); w += blockDim.x) dst[w] = src[w];
+  }
   const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
 #pragma unroll
   for (int k = 0; k < kClearRanges; ++k)
@@ -1336,13 +1354,12 @@ __global__ __launch_bounds__(kBlock) PROBE(__attribute__((amdgpu_waves_per_eu(ST
 // ---------------------------------------------------------------------------
 constexpr int kReduceChunk = 1024;  // triangles per workgroup
 
-// Sums of one query's triangles [chunk] over `copies` copies, `stride` words apart, into its totals.
-__device__ __forceinline__ void reduce_one(const long long* __restrict__ tally, uint32_t copies, uint64_t stride,
-                                           uint32_t nt, long long* __restrict__ scal, uint32_t chunk) {
+// The workgroup's sums of triangles [t0, t1) over `copies` copies, `stride`
+// words apart: sum k for thread k < 7 (the others get 0).
+__device__ __forceinline__ long long sum_triangles(const long long* __restrict__ tally, uint32_t copies, uint64_t stride,
+                                                   uint32_t t0, uint32_t t1) {
   __shared__ long long part[kBlock / 64][7];
   long long s[7] = {0, 0, 0, 0, 0, 0, 0};
-  const uint32_t t0 = chunk * kReduceChunk;
-  const uint32_t t1 = t0 + kReduceChunk < nt ? t0 + kReduceChunk : nt;
   // (triangle, copy) pairs over the lanes, so that small meshes with many copies use them all
   const uint32_t items = (t1 - t0) * copies;
   for (uint32_t i = threadIdx.x; i < items; i += kBlock) {
@@ -1356,11 +1373,19 @@ __device__ __forceinline__ void reduce_one(const long long* __restrict__ tally, 
 #pragma unroll
     for (int c = 0; c < 7; ++c) part[threadIdx.x >> 6][c] = s[c];
   __syncthreads();
-  if (threadIdx.x < 7) {
-    long long v = 0;
+  long long v = 0;
+  if (threadIdx.x < 7)
     for (int w = 0; w < kBlock / 64; ++w) v += part[w][threadIdx.x];
-    if (v) atomic_add_i64(scal + kFx + threadIdx.x, v);
-  }
+  return v;
+}
+
+// One query's triangles [chunk], added to its totals.
+__device__ __forceinline__ void reduce_one(const long long* __restrict__ tally, uint32_t copies, uint64_t stride,
+                                           uint32_t nt, long long* __restrict__ scal, uint32_t chunk) {
+  const uint32_t t0 = chunk * kReduceChunk;
+  const uint32_t t1 = t0 + kReduceChunk < nt ? t0 + kReduceChunk : nt;
+  const long long v = sum_triangles(tally, copies, stride, t0, t1);
+  if (threadIdx.x < 7 && v) atomic_add_i64(scal + kFx + threadIdx.x, v);
 }
 
 __global__ __launch_bounds__(kBlock) void reduce_batch_kernel(const QueryDev* __restrict__ qs,
@@ -1386,33 +1411,8 @@ __global__ __launch_bounds__(kBlock) void fold_tally_kernel(long long* __restric
 
 // F/q = K sum(w - w'), K = 2 Gamma_hat / (N S^2) (eq. drag with the effective
 // mass of Sec. II.A); moment about x_ref from the moment about the CV centre.
-// One workgroup per query: thread (c, k) adds up slot k of copies c, c + 8, ...
-// (consecutive words, so a copy is one load of half a wave), thread 0 converts.
-__global__ __launch_bounds__(kBlock) void finalize_kernel(const QueryDev* __restrict__ qs,
-                                                          const uint32_t* __restrict__ idx,
-                                                          const long long* __restrict__ scal_base, ScalCopies copies,
-                                                          double xr, double yr, double zr, double A_ref,
-                                                          ResultDev* __restrict__ out) {
-  constexpr uint32_t kRows = kBlock / kScalStride;
-  __shared__ long long part[kRows][kScalStride], s[kScalStride];
-  const uint32_t i = blockIdx.x, j = idx ? idx[i] : i;
-  const QueryDev& q = qs[j];
-  const uint32_t k = threadIdx.x % kScalStride, row = threadIdx.x / kScalStride;
-  long long v = row == 0 && k < (uint32_t)kScalarSlots ? scal_base[q.scalar_offset + k] : 0;
-  if (copies.base) {
-    const long long* c = copies.base + ((uint64_t)j << copies.log2) * kScalStride + k;
-#pragma unroll 8
-    for (uint32_t r = row; r < (1u << copies.log2); r += kRows) v += c[(uint64_t)r * kScalStride];
-  }
-  part[row][k] = v;
-  __syncthreads();
-  if (threadIdx.x < (uint32_t)kScalStride) {
-    v = 0;
-    for (uint32_t r = 0; r < kRows; ++r) v += part[r][threadIdx.x];
-    s[threadIdx.x] = v;
-  }
-  __syncthreads();
-  if (threadIdx.x != 0) return;
+__device__ __forceinline__ ResultDev converted(const QueryDev& q, const long long* s, double xr, double yr, double zr,
+                                               double A_ref) {
   const double N = (double)q.N;
   double F[3], Lc[3];
   for (int k = 0; k < 3; ++k) {
@@ -1454,7 +1454,53 @@ __global__ __launch_bounds__(kBlock) void finalize_kernel(const QueryDev* __rest
   r.tr_capped = (uint64_t)s[kTrCap];
   r.guard_trips = (uint64_t)s[kGuard];
   r.preculled = (uint64_t)s[kPreculled];
-  out[i] = r;
+  return r;
+}
+
+// One workgroup per query: thread (c, k) adds up slot k of copies c, c + 8, ...
+// (consecutive words, so a copy is one load of half a wave), thread 0 converts.
+// Meshes of at most kFinalizeTris triangles are summed here too (a launch of
+// its own took 4.6 us and the clearing of the totals before a plain run's as much;
+// 1280 triangles add 2 us here).
+__global__ __launch_bounds__(kBlock) void finalize_kernel(const QueryDev* __restrict__ qs,
+                                                          const uint32_t* __restrict__ idx,
+                                                          const long long* __restrict__ scal_base, ScalCopies copies,
+                                                          const long long* __restrict__ tally_base, TallyCopies tc,
+                                                          double xr, double yr, double zr, double A_ref,
+                                                          ResultDev* __restrict__ out) {
+  constexpr uint32_t kRows = kBlock / kScalStride;
+  __shared__ long long part[kRows][kScalStride], s[kScalStride];
+  __shared__ ResultDev rs;
+  const uint32_t i = blockIdx.x, j = idx ? idx[i] : i;
+  const QueryDev& q = qs[j];
+  const uint32_t k = threadIdx.x % kScalStride, row = threadIdx.x / kScalStride;
+  long long v = row == 0 && k < (uint32_t)kScalarSlots ? scal_base[q.scalar_offset + k] : 0;
+  if (copies.base) {
+    const long long* c = copies.base + ((uint64_t)j << copies.log2) * kScalStride + k;
+#pragma unroll 8
+    for (uint32_t r = row; r < (1u << copies.log2); r += kRows) v += c[(uint64_t)r * kScalStride];
+  }
+  part[row][k] = v;
+  long long tri = 0;  // thread c < 7: the query's total c
+  if (tally_base && q.per_tri) {
+    const long long* const base = tc.base ? tc.base : tally_base;
+    tri = sum_triangles(base + q.tally_offset, tc.base ? 1u << tc.log2 : 1u, tc.stride, 0, q.nt);
+  }
+  __syncthreads();
+  if (threadIdx.x < (uint32_t)kScalStride) {
+    v = 0;
+    for (uint32_t r = 0; r < kRows; ++r) v += part[r][threadIdx.x];
+    s[threadIdx.x] = v;
+  }
+  __syncthreads();
+  if (threadIdx.x < 7) s[kFx + threadIdx.x] += tri;
+  __syncthreads();
+  if (threadIdx.x == 0) rs = converted(q, s, xr, yr, zr, A_ref);
+  __syncthreads();
+  // one store of consecutive words (out may be host memory)
+  const uint64_t* const src = reinterpret_cast<const uint64_t*>(&rs);
+  uint64_t* const dst = reinterpret_cast<uint64_t*>(out + i);
+  if (threadIdx.x < (uint32_t)(sizeof(ResultDev) / 8)) dst[threadIdx.x] = src[threadIdx.x];
 }
 
 // Dynamic LDS of the tallies: the workgroup tally of lds_tris triangles, the
@@ -1627,6 +1673,15 @@ void clear_ranges(const ClearRanges& r, hipStream_t st) {
   if (n) clear_kernel<<<grid_for(n, 4096), kBlock, 0, st>>>(r);
 }
 
+void clear_and_upload(const ClearRanges& r, const QueryDev* h_qs, QueryDev* d_qs, uint32_t n, hipStream_t st) {
+  uint64_t most = 1;
+  for (int k = 0; k < kClearRanges; ++k) most = std::max(most, r.n[k]);
+  ArgQueries h;
+  std::memcpy(static_cast<void*>(&h), h_qs, n * sizeof(QueryDev));
+  std::memset(reinterpret_cast<char*>(&h) + n * sizeof(QueryDev), 0, (kArgQueries - n) * sizeof(QueryDev));
+  clear_upload_kernel<<<grid_for(most, 4096), kBlock, 0, st>>>(r, h, d_qs, n);
+}
+
 void zero_u32(uint32_t* p, uint64_t n, hipStream_t st) {
   if (n) zero_u32_kernel<<<grid_for(n, 4096), kBlock, 0, st>>>(p, n);
 }
@@ -1702,8 +1757,9 @@ void launch_fold_tally(long long* tally, const TallyCopies& copies, hipStream_t 
 }
 
 void launch_finalize(const QueryDev* d_qs, const uint32_t* d_idx, const long long* scal_base, const ScalCopies& copies,
-                     uint32_t nq, double xr, double yr, double zr, double A_ref, ResultDev* out, hipStream_t st) {
-  finalize_kernel<<<nq, kBlock, 0, st>>>(d_qs, d_idx, scal_base, copies, xr, yr, zr, A_ref, out);
+                     const long long* tally_base, const TallyCopies& tally_copies, uint32_t nq, double xr, double yr,
+                     double zr, double A_ref, ResultDev* out, hipStream_t st) {
+  finalize_kernel<<<nq, kBlock, 0, st>>>(d_qs, d_idx, scal_base, copies, tally_base, tally_copies, xr, yr, zr, A_ref, out);
 }
 
 // Per-triangle reduction of a list of slots (serving): entry y reduces slot idx[y].

@@ -102,6 +102,10 @@ struct ClearRanges {
   uint64_t n[kClearRanges];
 };
 void clear_ranges(const ClearRanges& r, hipStream_t st);
+// The same, and writes the n <= kArgQueries queries at h_qs (copied into the
+// launch's arguments) to d_qs: no copy, no host memory to keep, no wait.
+constexpr uint32_t kArgQueries = 4;
+void clear_and_upload(const ClearRanges& r, const QueryDev* h_qs, QueryDev* d_qs, uint32_t n, hipStream_t st);
 void zero_i64(long long* p, uint64_t n, hipStream_t st);
 // Fills the seeding start table of the current device (once per device).
 hipError_t init_seed_tables(hipStream_t st);
@@ -131,8 +135,12 @@ void launch_trace(const TraceArgs& a, uint32_t nq, uint64_t max_n, int stack_slo
 // Clears the queries' totals, then sums their triangles (plain path).
 void launch_reduce_totals(const QueryDev* d_qs, uint32_t nq, long long* tally_base, long long* scal_base,
                           uint32_t max_nt, hipStream_t st);
+// tally_base (null: none): per-triangle tallies that finalize sums itself, of
+// meshes of at most kFinalizeTris triangles (their queries' totals in scal are zero).
+constexpr uint32_t kFinalizeTris = 2048;
 void launch_finalize(const QueryDev* d_qs, const uint32_t* d_idx, const long long* scal_base, const ScalCopies& copies,
-                     uint32_t nq, double xr, double yr, double zr, double A_ref, ResultDev* out, hipStream_t st);
+                     const long long* tally_base, const TallyCopies& tally_copies, uint32_t nq, double xr, double yr,
+                     double zr, double A_ref, ResultDev* out, hipStream_t st);
 void launch_reduce_slots(const QueryDev* d_qs, const uint32_t* d_idx, uint32_t n, long long* tally_base,
                          long long* scal_base, uint32_t max_nt, hipStream_t st);
 // Launches at most max_grid workgroups over total_particles: no more than are
