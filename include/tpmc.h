@@ -322,7 +322,8 @@ void tpmc_destroy_server(tpmc_server s);
  * kernels, same results) in one call, with its workspace in a static device
  * array of the library, TPMC_NOALLOC_MAX_BYTES bytes on each GPU it runs on,
  * held until the process ends.  No device memory is allocated or freed.
- * Queries whose batch workspace (tpmc_batch_workspace_bytes) is larger are
+ * Queries whose batch workspace (tpmc_batch_workspace_bytes, less what it holds
+ * for speed alone: copies of the sums, latitude rows) is larger are
  * rejected with TPMC_E_WORKSPACE before any work is enqueued.  Every call on a
  * GPU uses that GPU's one array and leaves its contents behind (each call
  * clears what it accumulates into before its launch), so calls that overlap on
