@@ -22,7 +22,7 @@ LIB = os.path.join(HERE, "libtpmc.so")
 PROBE_LIB = os.path.join(HERE, "libtpmc_probe.so")
 PROBE_SOURCES = ["tpmc_capi.hip", "tpmc_kernels.hip"]  # the sources the probe switch changes
 SOURCES = ["tpmc_capi.hip", "tpmc_kernels.hip", "tpmc_bvh.hip", "tpmc_ceilings.hip"]
-HEADERS = ["tpmc_device.hpp", "tpmc_math.hpp", "tpmc_units.hpp", "tpmc_internal.h", "tpmc_launch.h"]
+HEADERS = ["tpmc_device.hpp", "tpmc_math.hpp", "tpmc_units.hpp", "tpmc_sah.hpp", "tpmc_internal.h", "tpmc_launch.h"]
 ARCH = os.environ.get("TPMC_OFFLOAD_ARCH", "gfx950")
 
 

@@ -11,6 +11,7 @@
 
 #include "tpmc_device.hpp"
 #include "tpmc_launch.h"
+#include "tpmc_sah.hpp"
 
 namespace tpmc {
 
@@ -442,9 +443,6 @@ __global__ void single_node_kernel(Node* nodes, const TriRec* tris) {
 // of kernels in the top five levels (1 to 16 workgroups), and 0.7 ms waiting
 // for the reads.  Build with supporting planes, before and now: 1k triangles
 // 0.67 and 0.48 ms, 20k 2.2 and 0.65, 50k 4.9 and 0.85, 500k 80.8 and 4.4.
-constexpr int kSahBins = 32;
-constexpr uint32_t kSahMaxLevel = 32;
-
 constexpr uint32_t kSahWave = 32;
 constexpr uint32_t kSahBig = 1024;
 constexpr uint32_t kSahChunk = 512;
@@ -475,17 +473,6 @@ struct SahState {
   uint32_t nsmall, depth, err;
 };
 
-// Order-preserving map of finite floats to int32 (for LDS integer min / max).
-__device__ __forceinline__ int f2o(float f) {
-  const int i = __float_as_int(f);
-  return i >= 0 ? i : i ^ 0x7FFFFFFF;
-}
-__device__ __forceinline__ float o2f(int i) { return __int_as_float(i >= 0 ? i : i ^ 0x7FFFFFFF); }
-
-__device__ __forceinline__ int sah_bin(float c, float cmin, float scale) {
-  return min(kSahBins - 1, (int)((c - cmin) * scale));
-}
-
 __device__ __forceinline__ float box_area(float lx, float ly, float lz, float hx, float hy, float hz) {
   const float ex = hx - lx, ey = hy - ly, ez = hz - lz;
   return ex * ey + ey * ez + ez * ex;
@@ -504,14 +491,6 @@ __device__ __forceinline__ void empty_box(int b[6]) {
 
 __device__ __forceinline__ float3 box_centre(const float4& lo, const float4& hi) {
   return make_float3(0.5f * (lo.x + hi.x), 0.5f * (lo.y + hi.y), 0.5f * (lo.z + hi.z));
-}
-
-// Whether axis k of a node can be binned, and the bins' origin and scale.
-__device__ __forceinline__ bool bin_axis(int cb_lo, int cb_hi, uint32_t level, float& cmin, float& scale) {
-  cmin = o2f(cb_lo);
-  const float ext = o2f(cb_hi) - cmin;
-  scale = (float)kSahBins / ext;
-  return level < kSahMaxLevel && ext > 0.0f && scale < __builtin_inff();
 }
 
 __device__ __forceinline__ Node make_node(const int L[6], const int R[6], int c0, int c1, int32_t parent) {
@@ -1117,10 +1096,9 @@ __global__ __launch_bounds__(kBlock) void sah_big_part_kernel(const float4* __re
 // and the sums of every plane run over the node's triangles one at a time (their
 // values in scalar registers), each lane summing for its own plane -- 32 planes
 // of two axes in a first pass, of the third in a second -- so no bins are kept
-// and no barrier is needed.  A pair needs no sums: every plane between its two
-// centres costs the same, so the lowest one of the first usable axis wins, with
-// the smaller centre on its left.  kSahWave: a wave takes longer the larger its
-// subtree (64: 267 us on the 50k satellite, one level launch of 25 us less).
+// and no barrier is needed.  A pair needs no sums (pair_plane).  kSahWave: a wave
+// takes longer the larger its subtree (64: 267 us on the 50k satellite, one level
+// launch of 25 us less).
 __global__ __launch_bounds__(kBlock) void sah_wave_kernel(const float4* __restrict__ plo,
                                                           const float4* __restrict__ phi,
                                                           const uint32_t* __restrict__ idx0,
@@ -1219,10 +1197,10 @@ __global__ __launch_bounds__(kBlock) void sah_wave_kernel(const float4* __restri
         const unsigned long long other = __shfl_xor(best, o);
         best = other < best ? other : best;
       }
-      else if (use[0] || use[1] || use[2]) {
-        const uint32_t k = use[0] ? 0u : (use[1] ? 1u : 2u);
-        best = k * kSahBins + 1u + min((uint32_t)__builtin_amdgcn_readlane((int)bins, s) >> (8u * k) & 255u,
-                                       (uint32_t)__builtin_amdgcn_readlane((int)bins, e) >> (8u * k) & 255u);
+      else {
+        const uint32_t plane = pair_plane((uint32_t)__builtin_amdgcn_readlane((int)bins, s),
+                                          (uint32_t)__builtin_amdgcn_readlane((int)bins, e));
+        if (plane != kNoPlane) best = plane;
       }
       const bool halve = best == ~0ull;  // uniform
       const uint32_t t = __builtin_amdgcn_readfirstlane((uint32_t)best);
