@@ -11,7 +11,6 @@
 
 #include "tpmc_device.hpp"
 #include "tpmc_launch.h"
-#include "tpmc_units.hpp"
 
 #ifndef TPMC_PHASE_PROBE
 #define TPMC_PHASE_PROBE 0
@@ -865,6 +864,9 @@ constexpr bool kWaveEntries = MODE == kTallyGlobal || MODE == kTallyLane || MODE
 
 constexpr uint32_t kNoEntry = 0xFFFFFFFFu;
 
+// Whether the launch's parts have workgroups that start on them (a whole batch).
+__device__ __forceinline__ bool starts_own(const BatchArgs& a) { return (a.start.own | a.start.div) != 0u; }
+
 // The cut of a part into units (tpmc_units.hpp).
 __device__ __forceinline__ UnitPlan unit_plan(const BatchArgs& a, uint32_t part) {
   const uint32_t j = part >> a.sub_log2, i = part & ((1u << a.sub_log2) - 1u);
@@ -872,8 +874,8 @@ __device__ __forceinline__ UnitPlan unit_plan(const BatchArgs& a, uint32_t part)
   const uint64_t e0 = a.entry_tile0 ? a.entry_tile0[j] * a.tile : 0ull;
   uint64_t e1 = a.entry_tiles ? e0 + a.entry_tiles[j] * a.tile : N;
   if (e1 > N) e1 = N;
-  const uint64_t ns = (uint64_t)(a.start_div + (part < a.start_rem ? 1u : 0u)) * (uint32_t)kWaves;
-  return unit_plan_of(e0, e1 > e0 ? e1 - e0 : 0ull, a.sub_log2, i, ns, a.share_log2, a.unit_cap_log2);
+  const uint64_t ns = (uint64_t)start_groups(a.start, part) * (uint32_t)kWaves;
+  return unit_plan_of(e0, e1 > e0 ? e1 - e0 : 0ull, a.sub_log2, i, ns, a.share_log2, a.unit_cap_log2, a.start_cap_log2);
 }
 
 // Claim a counted unit of the part (one atomic by lane 0; uniform result).
@@ -909,7 +911,7 @@ __device__ __forceinline__ uint32_t claim_any(const BatchArgs& a, uint32_t scan,
       const UnitPlan p = unit_plan(a, part);
       uint64_t x, y;
       has = counted_unit(p, __hip_atomic_load(&a.entry_next[part], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), x, y);
-      has = has && (a.start_div == 0u || y - x >= kJoinMin);
+      has = has && (!starts_own(a) || y - x >= kJoinMin);
     }
     uint64_t m = ballot(has);
     while (m != 0ull) {
@@ -922,26 +924,19 @@ __device__ __forceinline__ uint32_t claim_any(const BatchArgs& a, uint32_t scan,
   return kNoEntry;
 }
 
-// The part a workgroup starts on.  Workgroups are ordered by XCD, then (where
+// The workgroup's place in the dealing of parts.  Workgroups are ordered by XCD, then (where
 // the grid fills whole rounds of them) by compute unit, and the parts dealt to
 // them in that order, so that a compute unit's waves work on one query or few:
 // its rows of the latitude table (10 KB in reach of a query) stay in the
 // 32 KB L1.  (The hardware deals workgroups to the XCDs in turn, and within
 // an XCD to its compute units in turn; only speed depends on it.)
-__device__ __forceinline__ void start_part(const BatchArgs& a, uint32_t& part, uint32_t& rank) {
+__device__ __forceinline__ uint32_t dealt_place(const BatchArgs& a) {
   const uint32_t G = gridDim.x, x = blockIdx.x & 7u, y = blockIdx.x >> 3;
   const uint32_t rem8 = G & 7u, cus = a.xcd_cus;
   uint32_t i = x * (G >> 3) + (x < rem8 ? x : rem8);
   if (rem8 == 0u && (G >> 3) % cus == 0u) i += (y % cus) * ((G >> 3) / cus) + y / cus;
   else i += y;
-  const uint32_t more = a.start_rem * (a.start_div + 1u);  // the first start_rem parts have one workgroup more
-  if (i < more) {
-    part = i / (a.start_div + 1u);
-    rank = i % (a.start_div + 1u);
-  } else {  // start_div > 0 here
-    part = a.start_rem + (i - more) / a.start_div;
-    rank = (i - more) % a.start_div;
-  }
+  return i;
 }
 
 // The lane's particle of a batch.  Units begin at multiples of 64, so a batch
@@ -993,12 +988,28 @@ __global__ __launch_bounds__(kBlock) PROBE(__attribute__((amdgpu_waves_per_eu(ST
   __shared__ unsigned long long unit_sh[2];         // wave 0's claimed unit of the workgroup's part
   __shared__ unsigned long long w_next_sh[kWaves];  // each wave's next unclaimed particle
   __shared__ uint32_t part_sh;
+  // each wave's starting parts, in LDS rather than in registers through the trace
+  // loop: next and end of its own, the shared one (or kNone) and its rank there
+  __shared__ uint32_t own_sh[kWaves][4];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  // the part the workgroup starts on, and where its waves look for work
-  uint32_t scan, rank = kNone;  // rank: the workgroup's number among those that start on the part
-  if (a.start_div != 0u || a.start_rem != 0u) {
-    start_part(a, scan, rank);
+  // where the workgroup's waves look for work: its own parts first
+  uint32_t scan;
+  if (starts_own(a)) {
+    const uint32_t i = dealt_place(a);
+    uint32_t part = kNone, rank = 0u;
+    if (a.start.div != 0u) start_shared(a.start, i, part, rank);
+    scan = i * a.start.own;
+    if (lane == 0) {
+      own_sh[wave][0] = scan;
+      own_sh[wave][1] = scan + a.start.own;
+      own_sh[wave][2] = part;
+      own_sh[wave][3] = rank;
+    }
   } else {
+    if (lane == 0) {
+      own_sh[wave][0] = own_sh[wave][1] = 0u;
+      own_sh[wave][2] = kNone;
+    }
     const uint32_t x = blockIdx.x & 7u, lo = a.xcd_start[x], hi = a.xcd_start[x + 1];
     scan = (hi > lo ? lo + (blockIdx.x >> 3) % (hi - lo) : lo) << a.sub_log2;
     scan += (blockIdx.x >> 3) & ((1u << a.sub_log2) - 1u);
@@ -1030,18 +1041,25 @@ __global__ __launch_bounds__(kBlock) PROBE(__attribute__((amdgpu_waves_per_eu(ST
     uint32_t part;
     uint64_t p_begin = 0, p_end = 0;  // the wave's unit
     bool have = true;                 // the wave holds a unit of the part
-    if (rank != kNone) {
-      // the wave's starting unit; where the part is too small to have one for
-      // the workgroup, it has no counted units either
+    __builtin_amdgcn_wave_barrier();
+    const uint32_t wv = __builtin_amdgcn_readfirstlane(wave);
+    uint32_t own = __builtin_amdgcn_readfirstlane(own_sh[wv][0]), rank = 0u;
+    const bool alone = own != __builtin_amdgcn_readfirstlane(own_sh[wv][1]);
+    if (!alone) own = __builtin_amdgcn_readfirstlane(own_sh[wv][2]);
+    if (own != kNone) {
+      // the wave's starting unit of its next starting part; where the part is too
+      // small to have one for the workgroup, it has no counted units either
+      if (!alone) rank = __builtin_amdgcn_readfirstlane(own_sh[wv][3]);
+      if (lane == 0) own_sh[wv][alone ? 0 : 2] = alone ? own + 1u : kNone;
+      scan = own;
       const UnitPlan p = unit_plan(a, scan);
-      const uint64_t u = rank * (uint32_t)kWaves + (uint32_t)__builtin_amdgcn_readfirstlane(wave);
+      const uint64_t u = rank * (uint32_t)kWaves + wv;
       const uint64_t b = u << p.s_log2, e = (u + 1ull) << p.s_log2;
       const bool any = kWave ? b < p.n : ((uint64_t)(rank * (uint32_t)kWaves) << p.s_log2) < p.n;
       part = any ? scan : kNone;
       have = b < p.n;
       p_begin = p.lo + b;
       p_end = p.lo + (e < p.n ? e : p.n);
-      rank = kNone;
       if (part == kNone) continue;
     } else if (kWave) {
       part = claim_any(a, scan, p_begin, p_end);
@@ -1069,6 +1087,11 @@ __global__ __launch_bounds__(kBlock) PROBE(__attribute__((amdgpu_waves_per_eu(ST
         p_end = first + each < p_end ? first + each : p_end;
       }
     }
+    // wave-uniform: kept in scalar registers
+    p_begin = uniform_u64(p_begin);
+    p_end = uniform_u64(p_end);
+    part = __builtin_amdgcn_readfirstlane(part);
+    scan = __builtin_amdgcn_readfirstlane(scan);
     const uint32_t j = part == kNone ? kNone : part >> a.sub_log2;
     if (j != held && held != kNone) {
       // leaving the held query: flush its partial sums
@@ -1730,17 +1753,22 @@ void launch_batch(BatchArgs a, int stack_slots, TallyMode mode, uint64_t total_p
   resident = std::max(1, std::min(resident, mode == kTallyAuto ? 3 : 4));
   const uint64_t batches = (total_particles + 63) / 64;
   uint64_t grid = (uint64_t)n_cu * (uint64_t)std::min(groups_per_cu, resident);
-  grid = std::max<uint64_t>(1, std::min<uint64_t>(grid, (batches + kWaves - 1) / kWaves));
+  // no more than there are batches for, or, where queries are smaller, a workgroup for each
+  const uint64_t most = std::max<uint64_t>((batches + kWaves - 1) / kWaves, uniform ? a.n_entries : 1u);
+  grid = std::max<uint64_t>(1, std::min<uint64_t>(grid, most));
   const uint64_t waves = grid * kWaves;
   a.sub_log2 = 0;
   if (!uniform || batches > waves)  // more than one batch per wave: units are claimed, from up to 16 counters
     while (((uint64_t)a.n_entries << (a.sub_log2 + 1)) <= std::min<uint64_t>(counters, 16)) ++a.sub_log2;
   const uint64_t parts = (uint64_t)a.n_entries << a.sub_log2;
-  a.start_div = uniform ? (uint32_t)(grid / parts) : 0u;
-  a.start_rem = uniform ? (uint32_t)(grid % parts) : 0u;
+  a.start = uniform ? start_plan_of((uint32_t)grid, (uint32_t)parts) : StartPlan{0u, 0u, 0u, 0u};
   a.xcd_cus = (uint32_t)std::max(1, n_cu / 8);
   a.share_log2 = 6;
   while ((waves << (a.share_log2 + 1)) <= total_particles) ++a.share_log2;
+  // a workgroup's waves alone take the starting units of all its own parts: together at most a quarter of an equal
+  // share (a whole one: 3000 queries of 100 to 300000 particles on a cylinder 14.7 ms, 12.9 so)
+  a.start_cap_log2 = a.start.own == 0u ? 32u : a.share_log2 > 8u ? a.share_log2 - 8u : 0u;
+  for (uint32_t m = a.start.own; m != 0u && a.start_cap_log2 != 0u; m >>= 1) --a.start_cap_log2;
   a.unit_cap_log2 = 0;
   while ((128u << a.unit_cap_log2) <= a.tile / 4 && a.unit_cap_log2 < 8) ++a.unit_cap_log2;
   switch (stack_slots) {

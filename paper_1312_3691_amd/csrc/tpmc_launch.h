@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "tpmc_internal.h"
+#include "tpmc_units.hpp"
 
 namespace tpmc {
 
@@ -60,9 +61,9 @@ struct TraceArgs {
 // counter each (entry_next[j << sub_log2 | part]), so that the waves of a
 // launch with few queries do not all claim from one address (12 ns per atomic
 // on one address, measured).  A part is handed out in units of whole
-// 64-particle batches (UnitPlan in tpmc_kernels.hip): one unit per wave that
-// starts on it, taken without an atomic, then units by the counter that halve
-// in size towards the part's end.  A wave stays on one query and flushes its
+// 64-particle batches (UnitPlan in tpmc_units.hpp): one unit per wave that
+// starts on it (StartPlan there), taken without an atomic, then units by the counter
+// that halve in size towards the part's end.  A wave stays on one query and flushes its
 // partial sums only when it moves to another.  With workgroup LDS tallies the
 // workgroup's waves move to another part together.
 struct BatchArgs {
@@ -81,9 +82,8 @@ struct BatchArgs {
   uint32_t tile;                   // particles per tile (multiple of 64)
   uint32_t unit_cap_log2;          // no unit exceeds 64 << unit_cap_log2 particles (<= 8: 16-bit offsets in a unit)
   uint32_t share_log2;             // particles per wave of the whole launch (log2, rounded down)
-  // Starting parts taken without an atomic (0, 0: none): start_div workgroups
-  // start on each part, one more on each of the first start_rem.
-  uint32_t start_div, start_rem;
+  StartPlan start;                 // the parts that workgroups start on without an atomic (own 0, div 0: none)
+  uint32_t start_cap_log2;         // no starting unit exceeds 64 << start_cap_log2 particles
   uint32_t xcd_cus;                // compute units per XCD
   uint32_t lds_tris;               // largest nt of an entry with an LDS tally (kTallyLds / kTallyAuto)
   uint32_t wave_totals;            // kTallyAuto: some entry keeps totals only (per-wave LDS totals allocated)
@@ -143,10 +143,11 @@ void launch_finalize(const QueryDev* d_qs, const uint32_t* d_idx, const long lon
                      double zr, double A_ref, ResultDev* out, hipStream_t st);
 void launch_reduce_slots(const QueryDev* d_qs, const uint32_t* d_idx, uint32_t n, long long* tally_base,
                          long long* scal_base, uint32_t max_nt, hipStream_t st);
-// Launches at most max_grid workgroups over total_particles: no more than are
-// resident at once and no more than there are batches for.  uniform: every
-// entry may be started on without an atomic (a batch); sub_log2, the shares and
-// the starting parts of a are set here; counters: words at a.entry_next.
+// Launches at most groups_per_cu workgroups per compute unit over total_particles: no
+// more than are resident at once and no more than there are batches (or, in a batch,
+// queries) for.  uniform: every entry may be started on without an atomic (a
+// batch); sub_log2, the shares and the starting parts of a are set here; counters:
+// words at a.entry_next.
 void launch_batch(BatchArgs a, int stack_slots, TallyMode mode, uint64_t total_particles, bool uniform,
                   uint64_t counters, int n_cu, int groups_per_cu, hipStream_t st);
 // Check of the two-stage seeding's estimate (precull_check_kernel): out[0] the

@@ -11,6 +11,42 @@ namespace tpmc {
 
 __host__ __device__ inline uint32_t log2_floor(uint64_t v) { return 63u - (uint32_t)__builtin_clzll(v | 1ull); }
 
+// How the workgroups of a launch start: every part has workgroups of its own, so
+// that no part is left to be found by waves that look for one.  Each workgroup has
+// `own` consecutive parts, which it works off in turn; the parts from `shared` on,
+// fewer than there are workgroups, are started on by several each: div of them, one
+// more for the first rem.  With the parts beyond one per workgroup left to whoever
+// came first, all waves of a launch went for the same part, thousands of atomics on
+// its counter (20000 queries of 256 particles on a plate 430 ms, 0.8 now; 1500 of 1000
+// 8.5 ms, 0.2).  With the parts dealt out whole, some workgroups had one more than
+// others (1100 queries of 50000 on a cylinder 8.4 ms, 6.8 now).
+struct StartPlan {
+  uint32_t own, shared, div, rem;  // own 0, div 0: no workgroup has a part
+};
+
+__host__ __device__ inline StartPlan start_plan_of(uint32_t groups, uint32_t parts) {
+  const uint32_t own = parts / groups, left = parts % groups;
+  return StartPlan{own, own * groups, left ? groups / left : 0u, left ? groups % left : 0u};
+}
+
+// Workgroups that start on a part.
+__host__ __device__ inline uint32_t start_groups(const StartPlan& s, uint32_t part) {
+  return part < s.shared ? 1u : s.div + (part - s.shared < s.rem ? 1u : 0u);
+}
+
+// The shared part that workgroup i starts on (div > 0), and its number among the
+// part's workgroups; its own are [i * own, (i + 1) * own).
+__host__ __device__ inline void start_shared(const StartPlan& s, uint32_t i, uint32_t& part, uint32_t& rank) {
+  const uint32_t more = s.rem * (s.div + 1u);
+  if (i < more) {
+    part = s.shared + i / (s.div + 1u);
+    rank = i % (s.div + 1u);
+  } else {
+    part = s.shared + s.rem + (i - more) / s.div;
+    rank = (i - more) % s.div;
+  }
+}
+
 // One part's particles [lo, lo + n), in units of whole 64-particle batches:
 //  * ns starting units of s particles, the w-th for the w-th wave that starts
 //    on the part: no atomic, and at most half of an equal share each (the
@@ -37,9 +73,10 @@ struct UnitPlan {
 };
 
 // Part i of 2^sub_log2 of the entry [e0, e0 + all); ns starting waves; share
-// 2^share_log2 particles per wave of the launch; no unit above 64 2^cap_log2.
+// 2^share_log2 particles per wave of the launch; no unit above 64 2^cap_log2, no
+// starting unit above 64 2^start_cap_log2.
 __host__ __device__ inline UnitPlan unit_plan_of(uint64_t e0, uint64_t all, uint32_t sub_log2, uint32_t i, uint64_t ns,
-                                                 uint32_t share_log2, uint32_t cap_log2) {
+                                                 uint32_t share_log2, uint32_t cap_log2, uint32_t start_cap_log2 = 32u) {
   UnitPlan p;
   const uint64_t step = (((all + (1ull << sub_log2) - 1ull) >> sub_log2) + 63ull) & ~63ull;
   const uint64_t b = i * step < all ? i * step : all, e = (i + 1ull) * step < all ? (i + 1ull) * step : all;
@@ -51,6 +88,7 @@ __host__ __device__ inline UnitPlan unit_plan_of(uint64_t e0, uint64_t all, uint
     k = log2_floor(p.n) - log2_floor(ns * 128ull);
     if ((ns * 128ull) << k > p.n) --k;
     if (k > cap_log2) k = cap_log2;
+    if (k > start_cap_log2) k = start_cap_log2;
   }
   p.s_log2 = 6u + k;
   p.ns_end = ns << p.s_log2;
