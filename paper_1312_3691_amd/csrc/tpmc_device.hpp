@@ -616,16 +616,19 @@ __device__ __forceinline__ bool slab(const Ray& r, float lox, float loy, float l
 // root's boxes:
 //  * the fine latitude table (cubic in ln S, linear in the logit) leaves an
 //    error d in mu of about 1e-5; the speed's Halley step takes the table's
-//    4e-4 to about 1e-10 by its cubic convergence, plus the rounding of F, about
-//    3e-7 chi(s), over F'.  The estimate gives up (the particle is seeded
-//    exactly) where F' < chi / 100, which leaves 3e-5, and outside the tables'
-//    ranges of S and s;
+//    4e-4 to about 1e-10 by its cubic convergence, plus the rounding of F over F',
+//    e <= 1e-4 (speed_estimate32, which gives up where F' is too small: the
+//    particle is then seeded exactly, as outside the tables' ranges of S and s);
 //  * a latitude error d moves cos(phi) by d |mu| / cos(phi), so the estimate
 //    gives up for cos(phi) < 0.05 (mu within 1.25e-3 of +-1); elsewhere the
-//    point and the direction move by at most ~20 d, relative to r and to |w|;
-//  * along the at most 2 r of path inside the CV, the estimated ray then stays
-//    within ~60 d r plus twice the speed's relative error of the exact one: a few
-//    hundredths of the margin (0.02 r).
+//    point moves by at most 20 d r, and the velocity by at most 20 d (|w| + S) + e,
+//    and by 2e-4 for the Gaussians' radius, whose draw is rounded to 24 bits next to 1;
+//  * the direction moves by that over |w|, so the estimate also gives up for
+//    |w| < sqrt(1 + S^2) / 20 (a few particles in a million): by 7e-3 at most;
+//  * along the at most 2 r of path inside the CV the estimated ray then stays
+//    within 1.5e-2 r of the exact one, less than the margin (0.02 r).  Measured over
+//    2e8 particles at each of sixteen S: 0.14 of the margin at S = 0 (the radius),
+//    0.08 at 0.25, 0.016 at 1, 0.024 and less from 1.5 to 10.
 // tpmc_precull_check measures the distance between estimated and exact rays.
 // Box control volumes are not estimated.
 //
@@ -651,21 +654,14 @@ __device__ inline bool precull_estimate(const QueryDev& q, const float* __restri
   const float ua = unif32_hi(r0.a), uam = unif32_hi(~r0.a);  // u and 1 - u
   const float mu = q.s_zero ? 2.0f * ua - 1.0f : latitude_fine(q, lat_tab, lat_own, ua, uam);
   const float cphi = __builtin_amdgcn_sqrtf(fmaxf(0.0f, 1.0f - mu * mu));
-  // inward normal speed at s = S mu: F(x) - u chi at the tabulated start, with
-  // erf(x - s) + erf(s) from the two small erfc values, and one Halley step
+  // inward normal speed at s = S mu
   const float s = q.s_zero ? 0.0f : q.Sf * mu;
   const float fs = (s - kVnS0) * (1.0f / kVnDS);
   const float uc = unif32_hi(r0.c);
   float wn = normal_speed_table(vn_tab, fminf(fmaxf(fs, 0.0f), (float)(kVnNS - 1)),
                                 normal_speed_column(uc, unif32_hi(~r0.c)));
-  const float es2 = __expf(-s * s), ta = es2 * erfcx32(fabsf(s));
-  const float chi = fmaf((float)kSqrtPi * s, s >= 0.0f ? 2.0f - ta : ta, es2);
-  const float x = wn - s, ea = __expf(-x * x), tx = ea * erfcx32(fabsf(x));
-  const float esum = s < 0.0f ? ta - tx : (x < 0.0f ? tx - ta : 2.0f - tx - ta);
-  const float F = fmaf((float)kSqrtPi * s, esum, es2 - ea) - uc * chi, dF = 2.0f * wn * ea;
-  const float d2F = 2.0f * ea * (1.0f - 2.0f * wn * x);
-  wn -= 2.0f * F * dF * __builtin_amdgcn_rcpf(2.0f * dF * dF - F * d2F);
-  const bool ok = cphi >= 0.05f && fs >= 0.0f && fs <= (float)(kVnNS - 1) && dF >= 0.01f * chi;
+  bool ok = speed_estimate32(s, uc, wn);
+  ok = ok && cphi >= 0.05f && fs >= 0.0f && fs <= (float)(kVnNS - 1);
   // tangential Gaussians (Box-Muller, deviation 1 / sqrt 2) and the angles; v_sin / v_cos take revolutions
   const float rad = __builtin_amdgcn_sqrtf(-hw_ln(unif32_hi(r0.d)));
   const float ub = unif32_hi(r1.a), uth = unif32_hi(r0.b);
@@ -683,7 +679,9 @@ __device__ inline bool precull_estimate(const QueryDev& q, const float* __restri
     o[i] = fmaf(oU, q.Uf[i], fmaf(o1, q.e1f[i], fmaf(o2, q.e2f[i], q.c0f[i])));
     w[i] = fmaf(wU, q.Uf[i], fmaf(w1, q.e1f[i], w2 * q.e2f[i]));
   }
-  return ok;
+  // |w| >= sqrt(1 + S^2) / 20
+  const float least = 0.05f * q.Sf;
+  return ok && fmaf(wU, wU, fmaf(w1, w1, w2 * w2)) >= fmaf(least, least, 0.0025f);
 }
 
 // Whether a ray passes a box given by centre and half extents, t >= 0 (the

@@ -161,6 +161,37 @@ __host__ __device__ inline float erfcx32(float y) {
 #endif
 }
 
+// The seeding estimate's normal speed: one Halley step from the tabulated start x
+// towards the root of F(x | s) = u chi(s), with erf(x - s) + erf(s) from the two
+// small erfc values; false where the rounding of F may move the root too far.  F
+// and chi are sums of terms up to max(chi, exp(-s^2)) (for s < 0 differences:
+// chi is about exp(-s^2) / (2 s^2) there), rounded by up to 5e-7 of that: erfcx's
+// 3e-7 and a few products.  (The exponentials' own error, 1e-6 for arguments of
+// 16, multiplies the differences.)  F' of at least a two-hundredth of it leaves
+// 1e-4 in x.  F' >= chi / 100, the bound before, left 2e-2 at s = -4 (a CPU test
+// walks s and the draws).
+__host__ __device__ inline bool speed_estimate32(float s, float u, float& x) {
+  const float kRootPi = 0x1.c5bf8ap+0f;
+#ifdef __HIP_DEVICE_COMPILE__
+  const float es2 = __expf(-s * s), d = x - s, ea = __expf(-d * d);
+#else
+  const float kLog2e = 0x1.715476p+0f, d = x - s;
+  const float es2 = exp2f(-s * s * kLog2e), ea = exp2f(-d * d * kLog2e);
+#endif
+  const float ta = es2 * erfcx32(fabsf(s)), tx = ea * erfcx32(fabsf(d));
+  const float chi = fmaf(kRootPi * s, s >= 0.0f ? 2.0f - ta : ta, es2);
+  const float esum = s < 0.0f ? ta - tx : (d < 0.0f ? tx - ta : 2.0f - tx - ta);
+  const float F = fmaf(kRootPi * s, esum, es2 - ea) - u * chi, dF = 2.0f * x * ea;
+  const float d2F = 2.0f * ea * (1.0f - 2.0f * x * d);
+  const float den = 2.0f * dF * dF - F * d2F;
+#ifdef __HIP_DEVICE_COMPILE__
+  x -= 2.0f * F * dF * __builtin_amdgcn_rcpf(den);
+#else
+  x -= 2.0f * F * dF / den;
+#endif
+  return dF >= 0.005f * fmaxf(chi, es2);
+}
+
 }  // namespace tpmc
 
 #endif  // TPMC_MATH_HPP
