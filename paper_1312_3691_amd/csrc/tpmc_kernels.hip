@@ -1793,7 +1793,14 @@ void launch_fold_tally(long long* tally, const TallyCopies& copies, hipStream_t 
 void launch_finalize(const QueryDev* d_qs, const uint32_t* d_idx, const long long* scal_base, const ScalCopies& copies,
                      const long long* tally_base, const TallyCopies& tally_copies, uint32_t nq, double xr, double yr,
                      double zr, double A_ref, ResultDev* out, hipStream_t st) {
-  finalize_kernel<<<nq, kBlock, 0, st>>>(d_qs, d_idx, scal_base, copies, tally_base, tally_copies, xr, yr, zr, A_ref, out);
+  // in chunks: a launch holds fewer than 2^32 threads, 2^24 workgroups
+  for (uint32_t i = 0; i < nq; i += kMaxFinalize) {
+    ScalCopies c = copies;
+    if (c.base && !d_idx) c.base += ((uint64_t)i << c.log2) * kScalStride;
+    finalize_kernel<<<std::min(kMaxFinalize, nq - i), kBlock, 0, st>>>(d_idx ? d_qs : d_qs + i, d_idx ? d_idx + i : nullptr,
+                                                                     scal_base, c, tally_base, tally_copies, xr, yr, zr,
+                                                                     A_ref, out + i);
+  }
 }
 
 // Per-triangle reduction of a list of slots (serving): entry y reduces slot idx[y].

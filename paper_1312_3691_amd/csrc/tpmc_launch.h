@@ -138,6 +138,7 @@ void launch_reduce_totals(const QueryDev* d_qs, uint32_t nq, long long* tally_ba
 // tally_base (null: none): per-triangle tallies that finalize sums itself, of
 // meshes of at most kFinalizeTris triangles (their queries' totals in scal are zero).
 constexpr uint32_t kFinalizeTris = 2048;
+constexpr uint32_t kMaxFinalize = 65536;  // queries of one launch, a workgroup each
 void launch_finalize(const QueryDev* d_qs, const uint32_t* d_idx, const long long* scal_base, const ScalCopies& copies,
                      const long long* tally_base, const TallyCopies& tally_copies, uint32_t nq, double xr, double yr,
                      double zr, double A_ref, ResultDev* out, hipStream_t st);

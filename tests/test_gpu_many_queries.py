@@ -44,3 +44,21 @@ def test_batch_equals_plain(ctx, T, kind, totals, sizes):
                 assert np.array_equal(np.asarray(p[k]), np.asarray(g[k]), equal_nan=True), (kind, totals, sizes, i, k)
     b.close()
     mesh.close()
+
+
+def test_more_queries_than_one_launch_of_a_stage_takes(ctx, T):
+    """70001 queries: the plain path's stages and the finalisation run in chunks."""
+    mesh = ctx.build_mesh(*I.plate())
+    qs = [I.query(S=2.0 + i % 9, alpha=0.9, n=1 + i % 3, seed=i) for i in range(70_001)]
+    plain, pr = T.run(mesh, qs, A_ref=1.0)
+    pr.close()
+    b = T.Batch(mesh, qs)
+    got = b.launch().results(A_ref=1.0)
+    assert len(got) == len(plain) == len(qs)
+    for i, (q, p, g) in enumerate(zip(qs, plain, got)):
+        assert p["rays"] == g["rays"] == q["n"], i
+        for k in ("CD", "hits", "missed", "segments", "escaped", "Qhat"):
+            assert p[k] == g[k], (i, k)
+        assert (p["F_over_q"] == g["F_over_q"]).all(), i
+    b.close()
+    mesh.close()
