@@ -1745,12 +1745,11 @@ void launch_trace(const TraceArgs& a, uint32_t nq, uint64_t max_n, int stack_slo
 
 void launch_batch(BatchArgs a, int stack_slots, TallyMode mode, uint64_t total_particles, bool uniform,
                   uint64_t counters, int n_cu, int groups_per_cu, hipStream_t st) {
-  // workgroups resident per CU: at most four (four waves per SIMD at <= 128
-  // VGPRs; the mixed variant's 129-133 leave three), and what 160 KB of LDS holds
+  // workgroups resident per CU: at most four (four waves per SIMD, every instance
+  // has at most 128 VGPRs), and what 160 KB of LDS holds
   const size_t lds = tally_lds_bytes(mode, a.lds_tris, true, a.wave_totals != 0u) + (size_t)stack_slots * kBlock * 4 +
-                     (stack_slots <= 32 ? 7808u : 6784u);  // stack; queue, rings and claims of batch_kernel
-  int resident = (int)((160u << 10) / lds);
-  resident = std::max(1, std::min(resident, mode == kTallyAuto ? 3 : 4));
+                     (stack_slots <= 32 ? kBatchLdsPrecull : kBatchLds);
+  const int resident = std::max(1, std::min((int)((160u << 10) / lds), 4));
   const uint64_t batches = (total_particles + 63) / 64;
   uint64_t grid = (uint64_t)n_cu * (uint64_t)std::min(groups_per_cu, resident);
   // no more than there are batches for, or, where queries are smaller, a workgroup for each

@@ -10,6 +10,16 @@
 
 namespace tpmc {
 
+// Static LDS of batch_kernel beside its traversal stack, at most (queue, rings,
+// claims): stacks of up to 32 slots, which have the survivor rings, and larger
+// ones.  A host test holds the compiled kernels to it; 32 slots with their tallies
+// fit four times into a compute unit's 160 KB by 160 bytes each.
+constexpr uint32_t kBatchLdsPrecull = 7808, kBatchLds = 6784;
+
+}  // namespace tpmc
+
+namespace tpmc {
+
 // Tally strategy of the trace kernels.
 // Auto: per query, global per-triangle atomics or register totals (serving steps
 // that mix both kinds of request).
