@@ -1502,7 +1502,7 @@ hipError_t build_bvh_sah(const float* d_xyz, const uint32_t* d_tri, uint64_t nt6
     }
     for (uint32_t l = 0; l < mid_burst; ++l, ++mid)
       sah_level_kernel<<<gm, kBlock, 0, st>>>(x.plo, x.phi, x.idx[0], x.idx[1], x.order, x.mid[mid & 1u],
-                                              x.mid[mid & 1u ^ 1u], x.small, mid % 3u, x.st, d_nodes);
+                                              x.mid[(mid & 1u) ^ 1u], x.small, mid % 3u, x.st, d_nodes);
     sah_wave_kernel<<<gw, kBlock, 0, st>>>(x.plo, x.phi, x.idx[0], x.idx[1], x.order, x.small, x.st, d_nodes);
     pack_tris_kernel<<<g, kBlock, 0, st>>>(d_xyz, d_tri, x.order, nt, d_tris, d_orig);
     SahState h{};
