@@ -2,8 +2,10 @@
 
 The three launch parameters of the persistent launches (tpmc_set_tuning) -- refill_lanes
 (how few lanes of a wave may still be traversing before the lanes whose ray
-segment ended are served together), tile_particles (particles per work tile
-a workgroup claims) and groups_per_cu (persistent workgroups per compute unit)
+segment ended are served together), tile_particles (a batch: no wave takes more than
+a quarter of it at a time; a server: particles per tile of a step) and groups_per_cu
+(cap of the workgroups per compute unit; at most RESIDENT are ever launched, so
+values from there on are one setting, of which `tune` measures one)
 -- change only speed: particles are independent (Sec. II.A), each draws from
 its own counter-based stream, and all sums are exact integers, so every
 setting returns bit-identical results.  The best setting depends on the mesh
@@ -26,6 +28,7 @@ from typing import Callable, Dict, Iterable, List, Sequence, Tuple
 REFILL = (16, 24, 32, 40, 48)
 TILE = (4096, 16384, 65536)
 GROUPS = (4, 8, 16)
+RESIDENT = 4  # workgroups per compute unit that a persistent launch holds at most
 DEFAULT = {"refill_lanes": 32, "tile_particles": 16384, "groups_per_cu": 8}
 AXES: Tuple[Tuple[str, Sequence[int]], ...] = (("refill_lanes", REFILL), ("tile_particles", TILE),
                                               ("groups_per_cu", GROUPS))
@@ -89,6 +92,21 @@ def free_axes(fixed: Dict[str, int] = None) -> List[Tuple[str, Sequence[int]]]:
     return [(name, values) for name, values in AXES if name not in fixed]
 
 
+def launched_apart(axes: Sequence[Tuple[str, Sequence[int]]], start: Dict[str, int]) -> List[Tuple[str, Sequence[int]]]:
+    """The axes without values of groups_per_cu that launch what the start's or an earlier value does."""
+    out = []
+    for name, values in axes:
+        if name == "groups_per_cu":
+            seen, kept = {min(start[name], RESIDENT)}, []
+            for v in values:
+                if min(v, RESIDENT) not in seen:
+                    seen.add(min(v, RESIDENT))
+                    kept.append(v)
+            values = kept
+        out.append((name, values))
+    return out
+
+
 def tune(mesh, queries: Sequence[dict], particles: int = None, reps: int = 1,
          check_results: bool = True, fixed: Dict[str, int] = None) -> Tuple[Dict[str, int], List[Trial]]:
     """Measure the batched launch of `queries` (reduced to about `particles`
@@ -128,6 +146,7 @@ def tune(mesh, queries: Sequence[dict], particles: int = None, reps: int = 1,
         return ms
 
     fixed = dict(fixed or {})
-    best, trials = coordinate_search(cost, start=dict(ctx.tuning, **fixed), axes=free_axes(fixed))
+    start = dict(ctx.tuning, **fixed)
+    best, trials = coordinate_search(cost, start=start, axes=launched_apart(free_axes(fixed), start))
     ctx.set_tuning(**best)
     return best, trials
