@@ -229,7 +229,10 @@ __global__ void pack_tris_kernel(const float* __restrict__ xyz, const uint32_t* 
 // 4096 vertices) pairs, a wave each with the lanes over the vertices.  Bound:
 // FP64 issue of the second pass.  One lane per triangle over all vertices took
 // 900 us on the 50k-triangle satellite (196 workgroups, no early end) and 55 ms
-// on the 500k one.
+// on the 500k one.  Up to kSupportAll vertices the first pass looks at all of them
+// and is the only one: the second's launch and the list's clearing cost as much (LBVH
+// builds of 64 soup triangles 226 us with them, 202 without, 642 sphere vertices 279
+// and 272).
 struct SupportPlane {
   double ox, oy, oz, nx, ny, nz, tol;
   bool area;  // zero-area triangles are never hit and keep no flag
@@ -262,17 +265,26 @@ __device__ __forceinline__ uint32_t support_keep(bool above, bool below) {
   return ~((above ? 1u << 30 : 0u) | (below ? 1u << 31 : 0u));
 }
 
-constexpr uint32_t kSupportSpread = 256, kSupportSegment = 4096, kSupportTris = 4;
+constexpr uint32_t kSupportAll = 1024, kSupportSpread = 256, kSupportSegment = 4096, kSupportTris = 4;
 
 __global__ __launch_bounds__(kBlock) void support_spread_kernel(const float* __restrict__ xyz, uint32_t nv,
                                                                 const TriRec* __restrict__ tris, uint32_t nt,
                                                                 uint32_t* __restrict__ orig,
                                                                 uint32_t* __restrict__ list,
-                                                                uint32_t* __restrict__ n_list) {
-  __shared__ float v[kSupportSpread][3];
-  const uint32_t m = nv < kSupportSpread ? nv : kSupportSpread;
-  for (uint32_t i = threadIdx.x; i < m; i += kBlock) {
-    const uint64_t at = (uint64_t)i * nv / m;
+                                                                uint32_t* __restrict__ n_list,
+                                                                const Node* __restrict__ nodes,
+                                                                const uint32_t* __restrict__ depth,
+                                                                BuildRead* __restrict__ read) {
+  __shared__ float v[kSupportAll][3];
+  if (blockIdx.x == 0) {  // what the host reads of the build, side by side for one copy
+    const uint32_t* const root = reinterpret_cast<const uint32_t*>(nodes);
+    uint32_t* const out = reinterpret_cast<uint32_t*>(&read->root);
+    if (threadIdx.x < sizeof(Node) / 4u) out[threadIdx.x] = root[threadIdx.x];
+    else if (threadIdx.x == sizeof(Node) / 4u) read->depth = depth ? *depth : 0u;
+  }
+  const uint32_t m = nv <= kSupportAll ? nv : kSupportSpread;
+  for (uint32_t i = threadIdx.x; i < ((m + 15u) & ~15u); i += kBlock) {  // whole sixteens, with the last one again
+    const uint64_t at = m == nv ? min(i, m - 1u) : (uint64_t)i * nv / m;
     v[i][0] = xyz[3 * at];
     v[i][1] = xyz[3 * at + 1];
     v[i][2] = xyz[3 * at + 2];
@@ -282,11 +294,15 @@ __global__ __launch_bounds__(kBlock) void support_spread_kernel(const float* __r
   const bool on = k < nt;
   const SupportPlane p = support_plane(tris[on ? k : nt - 1u]);
   double hi = -__builtin_inf(), lo = __builtin_inf();
-  for (uint32_t j = 0; j < m; ++j) {
-    const double d = support_distance(p, v[j][0], v[j][1], v[j][2]);
-    hi = fmax(hi, d);
-    lo = fmin(lo, d);
-    if ((j & 15u) == 15u && __all(!on || !p.area || (hi > p.tol && lo < -p.tol))) break;
+  // sixteen at a time, so that their loads overlap
+  for (uint32_t j = 0; j < m; j += 16u) {
+#pragma unroll
+    for (uint32_t i = 0; i < 16u; ++i) {
+      const double d = support_distance(p, v[j + i][0], v[j + i][1], v[j + i][2]);
+      hi = fmax(hi, d);
+      lo = fmin(lo, d);
+    }
+    if (__all(!on || !p.area || (hi > p.tol && lo < -p.tol))) break;
   }
   const bool above = !p.area || hi > p.tol, below = !p.area || lo < -p.tol;
   if (on && (above || below)) orig[k] &= support_keep(above, below);
@@ -1337,16 +1353,19 @@ __global__ __launch_bounds__(kBlock) void sah_root_kernel(SahState* __restrict__
 }  // namespace
 
 void mark_support(const float* d_xyz, uint64_t nv, const TriRec* d_tris, uint64_t nt, uint32_t* d_orig,
-                  void* scratch, hipStream_t st) {
+                  const Node* d_nodes, const uint32_t* d_depth, BuildRead* d_read, void* scratch, hipStream_t st) {
   uint32_t* n_list = static_cast<uint32_t*>(scratch);
   uint32_t* list = n_list + 64;
-  zero_u32(n_list, 1, st);
-  support_spread_kernel<<<(uint32_t)((nt + kBlock - 1) / kBlock), kBlock, 0, st>>>(d_xyz, (uint32_t)nv, d_tris,
-                                                                                   (uint32_t)nt, d_orig, list, n_list);
+  if (nv > kSupportAll) zero_u32(n_list, 1, st);
+  support_spread_kernel<<<(uint32_t)((nt + kBlock - 1) / kBlock), kBlock, 0, st>>>(
+      d_xyz, (uint32_t)nv, d_tris, (uint32_t)nt, d_orig, list, n_list, d_nodes, d_depth, d_read);
+  if (nv <= kSupportAll) return;
   const uint64_t pairs = (nt + kSupportTris - 1) / kSupportTris * ((nv + kSupportSegment - 1) / kSupportSegment);
   support_kernel<<<(uint32_t)std::min<uint64_t>(2048, pairs / 4 + 1), kBlock, 0, st>>>(d_xyz, (uint32_t)nv, d_tris, d_orig,
                                                                                    list, n_list);
 }
+
+size_t support_scratch_bytes(uint64_t nt) { return (nt + 64) * sizeof(uint32_t); }
 
 size_t bvh_scratch_bytes(uint64_t nt) {
   const uint64_t nblocks = (nt + kSortTile - 1) / kSortTile;
@@ -1356,7 +1375,8 @@ size_t bvh_scratch_bytes(uint64_t nt) {
 
 hipError_t build_bvh(const float* d_xyz, const uint32_t* d_tri, uint64_t nt64, const float box_lo[3],
                      const float box_hi[3], void* scratch, Node* d_nodes, TriRec* d_tris, uint32_t* d_orig,
-                     uint32_t* h_depth, hipStream_t st) {
+                     uint32_t* h_depth, const uint32_t** d_depth, hipStream_t st) {
+  *d_depth = nullptr;
   const uint32_t nt = (uint32_t)nt64;
   const uint32_t nblocks = (nt + kSortTile - 1) / kSortTile;
   uint32_t* k0 = static_cast<uint32_t*>(scratch);
@@ -1388,8 +1408,7 @@ hipError_t build_bvh(const float* d_xyz, const uint32_t* d_tri, uint64_t nt64, c
   if (nt == 1) {
     single_node_kernel<<<1, 1, 0, st>>>(d_nodes, d_tris);
     *h_depth = 1;
-    e = hipStreamSynchronize(st);
-    return e != hipSuccess ? e : hipGetLastError();
+    return hipGetLastError();
   }
   zero_u32(flags, nt, st);
   zero_u32(depth, 1, st);
@@ -1399,10 +1418,8 @@ hipError_t build_bvh(const float* d_xyz, const uint32_t* d_tri, uint64_t nt64, c
   karras_kernel<<<gi, kBlock, 0, st>>>(k0, (int)nt, d_nodes, leaf_parent);
   refit_kernel<<<g, kBlock, 0, st>>>(d_nodes, leaf_parent, d_tris, nt, flags, nbox);
   depth_kernel<<<g, kBlock, 0, st>>>(d_nodes, leaf_parent, nt, depth);
-  e = hipMemcpyAsync(h_depth, depth, sizeof(uint32_t), hipMemcpyDeviceToHost, st);
-  if (e != hipSuccess) return e;
-  e = hipStreamSynchronize(st);
-  return e != hipSuccess ? e : hipGetLastError();
+  *d_depth = depth;
+  return hipGetLastError();
 }
 
 namespace {
@@ -1472,8 +1489,7 @@ hipError_t build_bvh_sah(const float* d_xyz, const uint32_t* d_tri, uint64_t nt6
     pack_tris_kernel<<<1, kBlock, 0, st>>>(d_xyz, d_tri, x.idx[0], 1u, d_tris, d_orig);
     single_node_kernel<<<1, 1, 0, st>>>(d_nodes, d_tris);
     *h_depth = 1;
-    e = hipStreamSynchronize(st);
-    return e != hipSuccess ? e : hipGetLastError();
+    return hipGetLastError();
   }
   sah_root_kernel<<<1, kBlock, 0, st>>>(x.st, x.big[0], x.mid[0], x.small, x.chunk_task[0], x.bins[0], nt);
   prim_box_kernel<<<g, kBlock, 0, st>>>(d_xyz, d_tri, nt, x.plo, x.phi, x.idx[0], x.order,

@@ -656,25 +656,35 @@ extern "C" tpmc_status tpmc_build_mesh_ex(tpmc_ctx ctx, const float* xyz, uint64
   void* scratch = nullptr;
   hipError_t e = hipMalloc(&d_xyz, 3 * nv * sizeof(float));
   if (e == hipSuccess) e = hipMalloc(&d_tri, 3 * nt * sizeof(uint32_t));
-  if (e == hipSuccess) e = hipMalloc(&scratch, builder == TPMC_BVH_SAH ? sah_scratch_bytes(nt) : bvh_scratch_bytes(nt));
+  // scratch: [what the host reads | supporting planes | build]
+  const uint64_t o_support = align256(sizeof(BuildRead)), o_build = o_support + align256(support_scratch_bytes(nt));
+  if (e == hipSuccess)
+    e = hipMalloc(&scratch, o_build + (builder == TPMC_BVH_SAH ? sah_scratch_bytes(nt) : bvh_scratch_bytes(nt)));
   if (e == hipSuccess) e = hipMalloc(&m->nodes, nnodes * sizeof(Node));
   if (e == hipSuccess) e = hipMalloc(&m->tris, nt * sizeof(TriRec));
   if (e == hipSuccess) e = hipMalloc(&m->orig, nt * sizeof(uint32_t));
   if (e == hipSuccess) e = hipMemcpyAsync(d_xyz, xyz, 3 * nv * sizeof(float), hipMemcpyHostToDevice, ctx->stream);
   if (e == hipSuccess) e = hipMemcpyAsync(d_tri, tri, 3 * nt * sizeof(uint32_t), hipMemcpyHostToDevice, ctx->stream);
   uint32_t depth = 0;
+  const uint32_t* d_depth = nullptr;
   if (e == hipSuccess) {
+    char* const at = static_cast<char*>(scratch) + o_build;
     const float lo[3] = {(float)m->lo[0], (float)m->lo[1], (float)m->lo[2]};
     const float hi[3] = {(float)m->hi[0], (float)m->hi[1], (float)m->hi[2]};
     e = builder == TPMC_BVH_SAH
-            ? build_bvh_sah(d_xyz, d_tri, nt, scratch, m->nodes, m->tris, m->orig, &depth, ctx->stream)
-            : build_bvh(d_xyz, d_tri, nt, lo, hi, scratch, m->nodes, m->tris, m->orig, &depth, ctx->stream);
+            ? build_bvh_sah(d_xyz, d_tri, nt, at, m->nodes, m->tris, m->orig, &depth, ctx->stream)
+            : build_bvh(d_xyz, d_tri, nt, lo, hi, at, m->nodes, m->tris, m->orig, &depth, &d_depth, ctx->stream);
   }
   if (e == hipSuccess) {
-    mark_support(d_xyz, nv, m->tris, nt, m->orig, scratch, ctx->stream);
-    e = hipMemcpyAsync(&m->root, m->nodes, sizeof(Node), hipMemcpyDeviceToHost, ctx->stream);
+    BuildRead* const d_read = static_cast<BuildRead*>(scratch);
+    mark_support(d_xyz, nv, m->tris, nt, m->orig, m->nodes, d_depth, d_read, static_cast<char*>(scratch) + o_support,
+                 ctx->stream);
+    BuildRead read{};
+    e = hipMemcpyAsync(&read, d_read, sizeof read, hipMemcpyDeviceToHost, ctx->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
     if (e == hipSuccess) e = hipGetLastError();
+    m->root = read.root;
+    if (d_depth) depth = read.depth;
   }
   if (d_xyz) (void)hipFree(d_xyz);
   if (d_tri) (void)hipFree(d_tri);

@@ -121,15 +121,22 @@ void zero_i64(long long* p, uint64_t n, hipStream_t st);
 hipError_t init_seed_tables(hipStream_t st);
 void zero_u32(uint32_t* p, uint64_t n, hipStream_t st);
 
-size_t bvh_scratch_bytes(uint64_t nt);
-// Supporting-plane flags in bits 30 / 31 of orig[] (after build_bvh; see
-// tpmc_bvh.hip); scratch: the build's (nt + 64 words are used).
+// What the host reads of a build.
+struct BuildRead {
+  Node root;
+  uint32_t depth;  // 0: the builder gave it
+};
+// Supporting-plane flags in bits 30 / 31 of orig[] (after a build; see
+// tpmc_bvh.hip), and the build's result at d_read (depth from d_depth unless null).
+size_t support_scratch_bytes(uint64_t nt);
 void mark_support(const float* d_xyz, uint64_t nv, const TriRec* d_tris, uint64_t nt, uint32_t* d_orig,
-                  void* scratch, hipStream_t st);
+                  const Node* d_nodes, const uint32_t* d_depth, BuildRead* d_read, void* scratch, hipStream_t st);
 constexpr uint32_t kOrigIdMask = 0x3FFFFFFFu;  // orig[] bits 0..29: original triangle index
+// Enqueued only; the depth is at *d_depth once the stream has run (null: *h_depth has it).
+size_t bvh_scratch_bytes(uint64_t nt);
 hipError_t build_bvh(const float* d_xyz, const uint32_t* d_tri, uint64_t nt, const float box_lo[3],
                      const float box_hi[3], void* scratch, Node* d_nodes, TriRec* d_tris, uint32_t* d_orig,
-                     uint32_t* h_depth, hipStream_t st);
+                     uint32_t* h_depth, const uint32_t** d_depth, hipStream_t st);
 
 // Top-down binned-SAH hierarchy in the same node / leaf format (default builder).
 size_t sah_scratch_bytes(uint64_t nt);
