@@ -167,8 +167,8 @@ typedef struct {
                               the persistent launches (batches and server steps); never more are
                               launched than can be resident at once (at most four) or have work */
   uint32_t plain_groups_per_cu; /* 0..32, default 4 (0 selects it): cap, in workgroups per compute
-                              unit, of the grid of tpmc_trace; the grid also keeps at least four
-                              particles per lane, so small queries get fewer workgroups */
+                              unit and query, of the grid of tpmc_trace; queries with fewer
+                              particles than lanes get fewer workgroups */
 } tpmc_tuning;
 
 /* Copy out / replace the context's tuning.  set validates every field
@@ -382,9 +382,9 @@ tpmc_status tpmc_ceiling_lds_atomic(tpmc_ctx ctx, void* dev_sink, uint32_t slots
  * [0, q->n_particles) of the query it returns the largest distance between
  * the estimated and the exact ray (|o_est - o| + 2 r |w_est/|w_est| - w/|w||)
  * as a fraction of the margin, over the particles the estimate covers (it
- * gives up near the poles mu = +-1, in the far tails of the normal speed and
- * outside its tables' ranges; those particles are always seeded exactly),
- * and their number.  Workspace: the
+ * gives up near the poles mu = +-1, in the far tails of the normal speed, for
+ * very slow particles and outside its tables' ranges; those particles are always
+ * seeded exactly), and their number.  Workspace: the
  * caller's device memory, >= TPMC_PRECULL_CHECK_BYTES, 256-byte aligned.
  * Synchronises the context's stream. */
 #define TPMC_PRECULL_CHECK_BYTES 1024

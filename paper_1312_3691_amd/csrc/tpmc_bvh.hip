@@ -457,11 +457,12 @@ __global__ void single_node_kernel(Node* nodes, const TriRec* tris) {
 // everything has been enqueued.  With one workgroup per
 // node and a host read per level, a 50k-triangle build spent 2.6 of its 3.2 ms
 // of kernels in the top five levels (1 to 16 workgroups), and 0.7 ms waiting
-// for the reads.  Build with supporting planes, before and now: 1k triangles
-// 0.67 and 0.48 ms, 20k 2.2 and 0.65, 50k 4.9 and 0.85, 500k 80.8 and 4.4.
+// for the reads.  Whole builds of satellites, before and now: 1k triangles 0.69
+// and 0.39 ms, 20k 2.25 and 0.66, 50k 4.9 and 1.05, 200k 24.6 and 2.1, 500k 81 and 4.4.
 constexpr uint32_t kSahWave = 32;
 constexpr uint32_t kSahBig = 1024;
 constexpr uint32_t kSahChunk = 512;
+static_assert(kSahBins == 32 && kSahWave <= 64, "sah_wave_kernel: a triangle per lane, 32 planes of two axes at a time");
 
 struct SahTask {
   uint32_t a, b, id;  // triangle positions [a, b] (b > a), node id
@@ -1105,7 +1106,7 @@ __global__ __launch_bounds__(kBlock) void sah_big_part_kernel(const float4* __re
   }
 }
 
-// ---- small nodes (m <= kSahWave <= 64): one wave per subtree, a triangle per lane ----
+// ---- small nodes (m <= kSahWave): one wave per subtree, a triangle per lane ----
 //
 // Lane l holds the triangle at position l of the subtree's range.  Nodes are
 // worked off one after another from a stack in LDS: the bounds of the centres

@@ -634,7 +634,7 @@ __device__ __forceinline__ bool slab(const Ray& r, float lox, float loy, float l
 //
 // Bound: VALU issue and the tables' gathers.  With two bracketed Halley steps,
 // the frame vector by vector, the box test bound by bound and eight gathers the
-// estimate was 525 vector instructions; 326 now, and two gathers.  Launch times
+// estimate was 525 vector instructions; 335 now, and two gathers.  Launch times
 // before and after: plate 60 x 1e6 1975 -> 1727 us, satellite 1024 x 1e6 62.8 ->
 // 58.7 ms, satellite 1e7 1380 -> 1330 us.
 // ---------------------------------------------------------------------------
